@@ -360,8 +360,10 @@ int rfo_set_moment_doubling(rfo_ctx *ctx, int enabled);
 
 /* Launch geometry and schedule of a context (for measurement; the defaults are the
  * measured best).  value = -1 restores the default.  Keys and accepted values:
- *   RFO_TUNE_PPL            probes per lane of the step kernels: 1, 2, 4
- *   RFO_TUNE_RPI            1x1: rows per wave iteration (1, 2, 7); 9x9: blocks per chunk (1, 2)
+ *   RFO_TUNE_PPL            1x1: probes per lane of the step kernels; FP64 and FP32 9x9: their probe
+ *                           columns per wave in units of 16 (1, 2, 4)
+ *   RFO_TUNE_RPI            1x1: rows per wave iteration (1, 2, 7); FP64 and FP32 9x9: probe tiles of
+ *                           one block row per workgroup (1, 2)
  *   RFO_TUNE_ROWS_PER_WG    block rows per scheduling unit of the step kernels (>= 1)
  *   RFO_TUNE_GRID           resident workgroups of the step kernels (>= 8, rounded to 8)
  *   RFO_TUNE_BF16_CHUNKS    BF16 steps: K chunks of 32 rows per iteration (1, 2)

@@ -172,6 +172,8 @@ inline int64_t tuned(const rfo_ctx *c, int key, int64_t def) {
   return c->tune[key] >= 0 ? c->tune[key] : def;
 }
 
+inline int kernel_precision(const rfo_ctx *c) { return c->prec == RFO_FP64 ? 0 : 1; }
+
 template <typename T>
 T *P(DevBuf &b) {
   return static_cast<T *>(b.p);
@@ -187,13 +189,32 @@ struct Plan {
   int ring;        // moment ring depth
   int rpi;         // rows per wave iteration
   int grid;        // resident workgroups of the step kernels
-  int n_pt_step;   // probe tiles of the step kernel (BF16: tiles of 16 * ntiles probes)
-  int ntiles;      // BF16: MFMA column tiles per wave
+  int n_pt_step;   // probe tiles of the step kernel (9x9: tiles of 16 * ntiles probes)
+  int ntiles;      // 9x9: MFMA column tiles per wave
+  int tpw;         // FP64/FP32 9x9: tiles of one block row per workgroup
+  int rows_step, n_rg_step;  // block rows per unit of the step kernels, and their units per tile
   size_t vec_elems;
   // bytes per vector slot: the vector, and in BF16 mode its BF16 copy (the
   // operand the steps gather) right after it
   size_t slot_bytes;
 };
+
+// Tiles of the FP64 and FP32 9x9 steps, in units of 16 probe columns per wave: 64 columns, narrower
+// where more than a quarter of the tiles would be padding or the waves would not fill the chip
+// (FP64, us per step at 64 / 32 / 16 columns: 55 / 60 / 83 on 4,000 atoms with 128 probes, 11.0 / 10.9
+// / 14 on 500 with 128, 10.0 / 7.6 / 6.9 on 55 with 64).  FP32 blocks that fill tiles of 256 columns
+// run on the vector units (16,000 atoms, 256 probes: 245 against 266 us; 4,000 atoms, 200 probes: 64
+// against 68, but 41 against 36 with 128 probes).
+inline int step9_tiles(const rfo_ctx *c) {
+  int nt = (int)tuned(c, RFO_TUNE_PPL, 0);
+  if (nt > 0) return nt;
+  auto tiles = [&](int t) { return (c->s + 16 * t - 1) / (16 * t); };
+  auto keep = [&](int t, int64_t waves) {
+    return 4 * c->s >= 3 * 16 * t * tiles(t) && c->nb * tiles(t) >= waves * c->cus;
+  };
+  if (c->prec == RFO_FP32 && c->sp % 256 == 0 && keep(16, 4)) return 16;
+  return keep(4, 8) ? 4 : keep(2, 2) ? 2 : 1;
+}
 
 inline Plan make_plan(const rfo_ctx *c) {
   Plan pl;
@@ -217,14 +238,14 @@ inline Plan make_plan(const rfo_ctx *c) {
   pl.n_rg = (int)((c->nb + rows - 1) / rows);
   pl.ring = 32;
   // 1x1 blocks: rows per wave iteration, or 7 when every row fits one chunk of 7
-  // neighbours (measured faster on the 7-point lattice); 9x9: blocks per chunk
-  pl.rpi = c->bd == 1 ? (c->max_row <= 7 ? 7 : 1) : 2;
-  {
-    const int r = (int)tuned(c, RFO_TUNE_RPI, pl.rpi);
-    if (r == 1 || r == 2 || (c->bd == 1 && r == 7)) pl.rpi = r;
-  }
+  // neighbours (measured faster on the 7-point lattice)
+  pl.rpi = (int)tuned(c, RFO_TUNE_RPI, c->max_row <= 7 ? 7 : 1);
   pl.n_pt_step = pl.n_pt;
   pl.ntiles = 0;
+  pl.tpw = 1;
+  pl.rows_step = pl.rows_per_wg;
+  pl.n_rg_step = pl.n_rg;
+  int64_t units = 0;
   int occ = 1;
   if (is_bf16(c->prec)) {
     // 4 MFMA column tiles (64 probes) per wave, one K chunk of 32 rows per
@@ -235,15 +256,28 @@ inline Plan make_plan(const rfo_ctx *c) {
     pl.n_pt_step = c->sp / (16 * pl.ntiles);
     pl.rpi = (int)tuned(c, RFO_TUNE_BF16_CHUNKS, pl.rpi);
     occ = std::max(1, rfo::step_bf16_blocks_per_cu(pl.ntiles, pl.rpi, c->prec == RFO_BF16X2 ? 1 : 0));
+  } else if (c->bd == 9) {
+    // tiles that hold no real probe are not run; with an overlap the CG kernels walk every
+    // column, so all tiles are
+    pl.ntiles = step9_tiles(c);
+    const int64_t cols = c->has_s ? c->sp : c->s;
+    pl.n_pt_step = (int)((cols + 16 * pl.ntiles - 1) / (16 * pl.ntiles));
+    // two tiles of a block row on a workgroup where they pair up (fewer rows in flight)
+    pl.tpw = pl.ntiles < 16 && pl.n_pt_step % 2 == 0 ? std::min((int)tuned(c, RFO_TUNE_RPI, 2), 2) : 1;
+    // one block row per row of waves: units so small that the rows in flight stay few
+    pl.rows_step = (int)tuned(c, RFO_TUNE_ROWS_PER_WG, 4 / pl.tpw);
+    pl.n_rg_step = (int)((c->nb + pl.rows_step - 1) / pl.rows_step);
+    units = (int64_t)((pl.n_pt_step + pl.tpw - 1) / pl.tpw) * pl.n_rg_step;
+    occ = std::max(1, rfo::step9_blocks_per_cu(kernel_precision(c), pl.ntiles));
   } else {
-    occ = std::max(1, rfo::step_blocks_per_cu(c->bd, c->prec == RFO_FP64 ? 0 : 1, pl.ppl, pl.rpi));
+    occ = std::max(1, rfo::step_blocks_per_cu(kernel_precision(c), pl.ppl, pl.rpi));
   }
   // one resident wave of workgroups, a multiple of 8 (one share per XCD), at
   // most four per CU: more workgroups widen the band of rows in flight on an XCD
   // past what its L2 holds of their neighbour rows (measured slower)
   int64_t grid = (int64_t)c->cus * std::min(occ, 4);
   grid = tuned(c, RFO_TUNE_GRID, grid);
-  const int64_t units = (int64_t)pl.n_pt_step * pl.n_rg;
+  if (units == 0) units = (int64_t)pl.n_pt_step * pl.n_rg;
   grid = std::min(grid, (units + 7) / 8 * 8);
   grid = std::max<int64_t>(8, grid / 8 * 8);
   pl.grid = (int)grid;
@@ -266,10 +300,11 @@ inline void fill_step(rfo_ctx *c, const Plan &pl, rfo::StepArgs &a) {
   a.rden = c->signs ? nullptr : P<double>(c->rden);
   a.nb = c->nb;
   a.sp = c->sp;
-  a.rows_per_wg = pl.rows_per_wg;
-  a.n_rg = pl.n_rg;
+  a.rows_per_wg = pl.rows_step;
+  a.n_rg = pl.n_rg_step;
   a.n_pt = pl.n_pt_step;
   a.rpi = pl.rpi;
+  a.tpw = pl.tpw;
   a.grid = pl.grid;
   // dense probes carry zero padding columns, and so does every vector made from them
   a.s_live = c->signs ? c->sp : (int)c->s;
@@ -288,8 +323,6 @@ inline void fill_init(rfo_ctx *c, const Plan &pl, rfo::InitArgs &a) {
   a.ppl = pl.ppl;
   a.grid = pl.grid;
 }
-
-inline int kernel_precision(const rfo_ctx *c) { return c->prec == RFO_FP64 ? 0 : 1; }
 
 // The segment gradient of the BF16 steps runs on the matrix cores when every real
 // probe has the same weight (the weight is applied in FP64 after each step's
@@ -358,7 +391,8 @@ inline hipError_t launch_any_step(const rfo_ctx *c, const Plan &pl, const rfo::S
     b.outb = static_cast<char *>(a.out) + pl.vec_elems * sizeof(float);
     return rfo::launch_step_bf16(pl.ntiles, b, c->stream);
   }
-  return rfo::launch_step(c->bd, kernel_precision(c), pl.ppl, b, c->stream);
+  if (c->bd == 9) return rfo::launch_step9(kernel_precision(c), pl.ntiles, b, c->stream);
+  return rfo::launch_step(kernel_precision(c), pl.ppl, b, c->stream);
 }
 
 // y = scale r into a vector slot (and its BF16 copy in BF16 mode)

@@ -54,9 +54,10 @@ struct StepArgs {
   int rows_per_wg;
   int n_rg, n_pt;
   int rpi;                 // 1x1 blocks: rows per wave iteration (1 or 2, 8 neighbours per
-                           // chunk) or 7 (one row, 7 neighbours per chunk); 9x9: blocks per chunk
+                           // chunk) or 7 (one row, 7 neighbours per chunk)
   int grid;                // workgroups (multiple of 8); part has [grid][sp]
   int reverse;             // sweep each XCD's range of units from its end
+  int tpw;                 // FP64/FP32 9x9 steps: probe tiles of a block row per workgroup (1, 2)
   int hsplit;              // BF16 steps: the pack holds hi and lo BF16 parts of H_hat
   // probe columns at or past s_live are zero in every input vector (dense probes,
   // whose padding columns are zero): a lane whose probes all lie there loads
@@ -73,7 +74,10 @@ inline int step_mode(const StepArgs &a) {
 }
 
 // precision: 0 = fp64 (double vectors, double H), 1 = fp32 (float vectors, float H)
-hipError_t launch_step(int bd, int precision, int ppl, const StepArgs &a, hipStream_t s);
+// launch_step: 1x1 blocks; launch_step9: 9x9 blocks, tiles of 16 * nt probe columns (a.n_pt of them;
+// columns past the last tile are not touched and get zero moment partials)
+hipError_t launch_step(int precision, int ppl, const StepArgs &a, hipStream_t s);
+hipError_t launch_step9(int precision, int nt, const StepArgs &a, hipStream_t s);
 
 // y = scale * r (+ acc = alpha * r, + part = r . y) with the step kernel's decomposition
 struct InitArgs {
@@ -95,7 +99,8 @@ struct InitArgs {
 };
 hipError_t launch_init(int precision, const InitArgs &a, hipStream_t s);
 // Resident workgroups per CU of the step kernel variant (0 on error).
-int step_blocks_per_cu(int bd, int precision, int ppl, int rpi);
+int step_blocks_per_cu(int precision, int ppl, int rpi);
+int step9_blocks_per_cu(int precision, int nt);
 // K rows per chunk of the BF16 MFMA step (the K of v_mfma_f32_16x16x32_bf16)
 constexpr int kKChunk = 32;
 // BF16 MFMA step for 9x9 blocks; a.hval holds the packed A operands
