@@ -153,6 +153,26 @@ int rfo_set_hamiltonian(rfo_ctx *ctx, int64_t n_block_rows, int block_dim, const
       HIPCHK(hipMemcpyAsync(ctx->nz_low.p, low.data(), low.size() * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream));
     ctx->n_up = (int64_t)up.size();
     ctx->n_low = (int64_t)low.size();
+    // 9x9 outer products: the blocks of a row (upper ones, and all) in groups of at most
+    // kSddmm9Group, as even as they go
+    std::vector<int64_t> gu(1, 0), ga(1, 0);
+    if (block_dim == 9) {
+      auto split = [](std::vector<int64_t> &g, int64_t n) {
+        const int64_t k = (n + rfo::kSddmm9Group - 1) / rfo::kSddmm9Group, q0 = g.back();
+        for (int64_t t = 1; t <= k; ++t) g.push_back(q0 + n * t / k);
+      };
+      for (int64_t I = 0; I < nb; ++I) {
+        const int32_t *b0 = col_idx + row_ptr[I], *b1 = col_idx + row_ptr[I + 1];
+        split(gu, b1 - std::lower_bound(b0, b1, (int32_t)I));
+        split(ga, b1 - b0);
+      }
+      TRY(ensure(ctx, ctx->grp_up, gu.size() * sizeof(int64_t)));
+      TRY(ensure(ctx, ctx->grp_all, ga.size() * sizeof(int64_t)));
+      HIPCHK(hipMemcpyAsync(ctx->grp_up.p, gu.data(), gu.size() * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream));
+      HIPCHK(hipMemcpyAsync(ctx->grp_all.p, ga.data(), ga.size() * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream));
+    }
+    ctx->n_grp_up = (int64_t)gu.size() - 1;
+    ctx->n_grp_all = (int64_t)ga.size() - 1;
 
     HIPCHK(hipStreamSynchronize(ctx->stream));  // host vectors go out of scope
   }
@@ -354,7 +374,7 @@ int density_sddmm(rfo_ctx *ctx, const void *xbase, double *G, int accumulate) {
   a.nzlist = nullptr;
   a.ppl = sddmm_ppl(ctx);
   a.s_live = (int)ctx->s;
-  HIPCHK(rfo::launch_sddmm(kernel_precision(ctx), a, ctx->stream));
+  HIPCHK(launch_outer(ctx, kernel_precision(ctx), a, ctx->stream));
   return RFO_OK;
 }
 

@@ -41,6 +41,9 @@ struct rfo_ctx {
   DevBuf up_grp;
   int64_t n_up_grp = 0;
   bool has_up_grp = false;
+  // 9x9 FP64/FP32 outer products: groups of the upper blocks and of all blocks
+  DevBuf grp_up, grp_all;
+  int64_t n_grp_up = 0, n_grp_all = 0;
   // BF16 steps: K chunks of 16 rows per block row (first chunk of each row,
   // gathered row J*9 + c and source nz*9 + c of every K row)
   DevBuf kc_ptr, kc_idx, kc_src;
@@ -95,7 +98,7 @@ struct rfo_ctx {
   ~rfo_ctx() {
     hipSetDevice(device);
     DevBuf *all[] = {&row_ptr, &col, &brow, &tpos, &hraw, &h64, &h32, &hbf16, &gscratch, &nz_up, &nz_low,
-                     &kc_ptr, &kc_idx, &kc_src, &up_grp,
+                     &kc_ptr, &kc_idx, &kc_src, &up_grp, &grp_up, &grp_all,
                      &s64, &cg_part, &cg_sc, &cg_spart, &GQ, &rat, &rat_part, &rat_sc, &rat_rho, &rat_coef,
                      &sgn, &rden, &w, &vec, &acc, &ring, &moments, &coef, &samples,
                      &costab, &small, &flags, &G, &dHdR, &forces};
@@ -334,15 +337,24 @@ inline bool use_mfma_sddmm(const rfo_ctx *c) {
   return tuned(c, RFO_TUNE_SDDMM_MFMA, 1) != 0;
 }
 
+// Outer products on the listed blocks (the upper blocks, or all without a list).
+inline hipError_t launch_outer(const rfo_ctx *c, int precision, const rfo::SddmmArgs &a, hipStream_t s) {
+  if (c->bd != 9) return rfo::launch_sddmm(precision, a, s);
+  rfo::SddmmArgs b = a;
+  b.grp = static_cast<const int64_t *>(a.nzlist ? c->grp_up.p : c->grp_all.p);
+  b.n_grp = a.nzlist ? c->n_grp_up : c->n_grp_all;
+  return rfo::launch_sddmm9(precision, b, c->cus, s);
+}
+
 // The segment gradient in launches of at most 32 steps each (8 for the BF16
 // kernel; RFO_TUNE_SDDMM_STEPS, RFO_TUNE_SDDMM_STEPS_BF16): all resident waves then work on the same few steps, so the
 // rows of X_t and Y_t that the blocks of a band of block rows share are read
-// while the L2 holds them.  Measured on the 16,000-atom cluster at 8000 terms
-// (segments of 64 steps).
+// while the L2 holds them.  (16,000 atoms, FP64, 256 probes, gradient of 130 terms at 8 / 16 / 32
+// steps: 146.9 / 143.2 / 143.4 ms; 2,000 atoms, 33 probes: 6.6 / 5.7 / 5.7.)
 inline hipError_t launch_sddmm_segment(const rfo_ctx *c, int precision, const rfo::SddmmArgs &a,
                                        size_t slot_bytes, hipStream_t s) {
   const int tg = (int)tuned(c, RFO_TUNE_SDDMM_STEPS, 32);
-  if (tg <= 0 || a.count <= tg) return rfo::launch_sddmm(precision, a, s);
+  if (tg <= 0 || a.count <= tg) return launch_outer(c, precision, a, s);
   rfo::SddmmArgs b = a;
   for (int t0 = 0; t0 < a.count; t0 += tg) {
     b.xbase = static_cast<const char *>(a.xbase) + (size_t)t0 * slot_bytes;
@@ -350,7 +362,7 @@ inline hipError_t launch_sddmm_segment(const rfo_ctx *c, int precision, const rf
     b.count = std::min(tg, a.count - t0);
     b.j0 = a.j0 + t0;
     b.accumulate = t0 == 0 ? a.accumulate : 1;
-    const hipError_t e = rfo::launch_sddmm(precision, b, s);
+    const hipError_t e = launch_outer(c, precision, b, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -727,11 +739,16 @@ struct ProbeBatches {
   }
 };
 
-// A last VALU probe tile of 128 columns that holds at most 64 real probes runs as a
-// batch of its own, 64 columns wide (a tile costs about the same whatever part of
-// it is live): the batches [0, s - r), [s - r, s), or none.
+// A last probe tile of 128 columns that holds at most 64 real probes runs as a batch of its own,
+// 64 columns wide: the batches [0, s - r), [s - r, s), or none.  1x1: a tile costs about the same
+// whatever part of it is live.  9x9: the tiles are narrower, and the batches pay only by the rows that
+// they keep out of the caches at a time (gradient, ms with and without: 16,000 atoms FP64, 140 probes
+// 45.7 and 53.6; 4,000 FP32, 288 probes 22.1 and 27.7; 6,000 FP32, 150 probes 20.5 and 19.8; 1,000 FP64,
+// 130 probes 6.2 and 5.6; 1,000 FP32, 190 probes 5.7 and 4.4): vectors under 16 MiB run whole.
 inline std::vector<std::pair<int64_t, int64_t>> last_tile_batches(const rfo_ctx *c) {
   if (c->has_s || is_bf16(c->prec) || c->s <= 128 || c->s % 128 == 0 || c->s % 128 > 64) return {};
+  const int64_t vec = c->nb * c->bd * (int64_t)c->sp * (c->prec == RFO_FP64 ? 8 : 4);
+  if (c->bd == 9 && vec < (int64_t)16 << 20) return {};
   const int64_t r = c->s % 128;
   return {{0, c->s - r}, {c->s - r, r}};
 }

@@ -277,7 +277,7 @@ int rfo_rational_estimate(rfo_ctx *ctx, double mu, int64_t n_poles, const double
     b.first = 0.5 * coef;  // the symmetric kernel adds X Y^T + Y X^T
     b.G = G;
     b.accumulate = acc;
-    HIPCHK(rfo::launch_sddmm(0, b, ctx->stream));
+    HIPCHK(launch_outer(ctx, 0, b, ctx->stream));
     return RFO_OK;
   };
   if (grad_s) {
@@ -299,7 +299,7 @@ int rfo_rational_estimate(rfo_ctx *ctx, double mu, int64_t n_poles, const double
     sa.first = poly[2];
     sa.G = P<double>(ctx->G);
     sa.accumulate = 0;
-    HIPCHK(rfo::launch_sddmm(0, sa, ctx->stream));
+    HIPCHK(launch_outer(ctx, 0, sa, ctx->stream));
   }
   // P r starts at f0 S^{-1} r
   if (dens) {
@@ -361,16 +361,16 @@ int rfo_rational_estimate(rfo_ctx *ctx, double mu, int64_t n_poles, const double
       sa.xbase = w.x;
       sa.ybase = w.x;
       sa.first = -2.0 * tr;
-      HIPCHK(rfo::launch_sddmm(0, sa, ctx->stream));
+      HIPCHK(launch_outer(ctx, 0, sa, ctx->stream));
       sa.xbase = w.x + plane;
       sa.ybase = w.x + plane;
       sa.first = 2.0 * tr;
-      HIPCHK(rfo::launch_sddmm(0, sa, ctx->stream));
+      HIPCHK(launch_outer(ctx, 0, sa, ctx->stream));
       sa.sym = 1;
       sa.xbase = w.x;
       sa.ybase = w.x + plane;
       sa.first = 2.0 * ti;
-      HIPCHK(rfo::launch_sddmm(0, sa, ctx->stream));
+      HIPCHK(launch_outer(ctx, 0, sa, ctx->stream));
       sa.sym = 0;
     }
   }
@@ -392,7 +392,7 @@ int rfo_rational_estimate(rfo_ctx *ctx, double mu, int64_t n_poles, const double
     sa.ybase = nullptr;
     sa.first = 1.0;
     sa.G = P<double>(db);
-    HIPCHK(rfo::launch_sddmm(0, sa, ctx->stream));
+    HIPCHK(launch_outer(ctx, 0, sa, ctx->stream));
     TRY(copy_out(ctx, density_out, db.p, gbytes));
     ctx->has_dens = !grad;
     if (ctx->has_s) {
@@ -405,7 +405,7 @@ int rfo_rational_estimate(rfo_ctx *ctx, double mu, int64_t n_poles, const double
       TRY(ensure(ctx, ctx->GQ, gbytes));
       sa.xbase = w.p;
       sa.G = P<double>(ctx->GQ);
-      HIPCHK(rfo::launch_sddmm(0, sa, ctx->stream));
+      HIPCHK(launch_outer(ctx, 0, sa, ctx->stream));
       ctx->has_q = true;
     }
   }

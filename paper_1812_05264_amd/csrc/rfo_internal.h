@@ -171,12 +171,20 @@ struct SddmmArgs {
   int accumulate;
   const int64_t *nzlist;   // blocks to compute (nullptr = all nnzb)
   int64_t nlist;
-  int ppl;                 // probes per lane per load (1 or 2)
+  const int64_t *grp;      // 9x9: groups of the blocks [n_grp + 1]
+  int64_t n_grp;
+  int spread;              // 9x9, set by the launch: items take their probes over several steps
+  int ppl;                 // 1x1: probes per lane per load (1 or 2)
   int sym;                 // G[nz] (+)= sum_t coef_t sum_c w_c (X_I Y_J^T + Y_I X_J^T)
   int s_live;              // columns at or past s_live have weight zero and are skipped
                            // (0 = none)
 };
+// launch_sddmm: 1x1 blocks; launch_sddmm9: 9x9 blocks in the n_grp groups grp (group g holds the
+// blocks nzlist[q], or q itself without a list, q in [grp[g], grp[g+1]): one block row each, 1 to
+// kSddmm9Group blocks); cus: compute units of the device
+constexpr int kSddmm9Group = 6;
 hipError_t launch_sddmm(int precision, const SddmmArgs &a, hipStream_t s);
+hipError_t launch_sddmm9(int precision, const SddmmArgs &a, int cus, hipStream_t s);
 
 // Symmetric segment gradient of the BF16 steps on the matrix cores, from the
 // vectors' BF16 copies, with one weight w0 for the first s_real probes and zero
@@ -190,6 +198,7 @@ constexpr int kSddmmGroup = 6;  // measured best (10: 22% slower)
 struct SddmmMfmaArgs {
   const int64_t *grp;      // [n_grp + 1]
   int64_t n_grp;
+  int spread;              // 9x9, set by the launch: items take their probes over several steps
   const int64_t *nzlist;
   const int64_t *brow;
   const int32_t *col;
