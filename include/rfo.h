@@ -376,9 +376,10 @@ int rfo_set_moment_doubling(rfo_ctx *ctx, int enabled);
  *   RFO_TUNE_OVERLAP        1: each segment's gradient of the doubled adjoint runs on a
  *                           second stream beside the next segment's steps (default 0; the
  *                           result is bitwise the serial one)
- *   RFO_TUNE_CPLX_PPL, RFO_TUNE_CPLX_ROWS, RFO_TUNE_CPLX_GRID  probes per lane (1, 2), rows
- *                           (1x1: 4, 8) or blocks (9x9: 1, 2) per chunk, and workgroups of
- *                           the complex shifted product of the rational estimate
+ *   RFO_TUNE_CPLX_PPL, RFO_TUNE_CPLX_ROWS, RFO_TUNE_CPLX_GRID  probes per lane (1x1: 1, 2) or
+ *                           tiles of 16 columns per wave (9x9: 1, 2), rows per chunk (1x1: 4,
+ *                           8) or tiles of a block row per workgroup (9x9: 1, 2), and workgroups
+ *                           of the complex shifted product of the rational estimate
  *   RFO_TUNE_ADJOINT_BYTES  memory budget (bytes) of rfo_energy_and_dEdH's vector slots
  *                           (default: 85% of the device memory free at the call plus what
  *                           the slots already hold); above it the probe columns run in

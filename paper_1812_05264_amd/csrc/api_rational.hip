@@ -18,8 +18,8 @@ struct CxWork {
   double *part, *part2;       // column partials
   double *sc;                 // CGLS scalars [7][sp] + resmax
   int nparts;                 // rows of part / part2
-  int ppl;                    // probes per lane of the complex product
-  int u;                      // neighbours (1x1) or blocks (9x9) per chunk
+  int ppl;                    // complex product, 1x1: probes per lane; 9x9: column tiles per wave
+  int u;                      // 1x1: neighbours per chunk
   rfo::CspArgs ca;            // complex product arguments (x, out, z, part set per launch)
 };
 
@@ -30,7 +30,8 @@ int cspmm(rfo_ctx *ctx, CxWork &w, const double *x, double *out, double zr, doub
   w.ca.zr = zr;
   w.ca.zi = zi;
   w.ca.part = part;
-  HIPCHK(rfo::launch_cspmm(ctx->bd, w.ppl, w.u, w.ca, ctx->stream));
+  if (ctx->bd == 9) HIPCHK(rfo::launch_cspmm9(w.ppl, w.ca, ctx->stream));
+  else HIPCHK(rfo::launch_cspmm(w.ppl, w.u, w.ca, ctx->stream));
   return RFO_OK;
 }
 
@@ -138,17 +139,6 @@ int rfo_rational_estimate(rfo_ctx *ctx, double mu, int64_t n_poles, const double
   // launch decomposition of the complex product: the step kernel's row groups
   const Plan pl = make_plan(ctx);
   CxWork w;
-  // two probes per lane where the tiles allow: one tile of 128 probes reads the
-  // H_hat blocks once per product (measured faster for 1x1 and 9x9 blocks)
-  w.ppl = sp % 128 == 0 ? 2 : 1;
-  // with an overlap the 9x9 product keeps four row sums per probe: one probe per lane
-  if (ctx->has_s && ctx->bd == 9) w.ppl = 1;
-  if (ctx->tune[RFO_TUNE_CPLX_PPL] >= 0) w.ppl = ctx->tune[RFO_TUNE_CPLX_PPL] == 2 && sp % 128 == 0 ? 2 : 1;
-  w.u = ctx->bd == 1 ? 4 : 1;
-  {
-    const int u = (int)tuned(ctx, RFO_TUNE_CPLX_ROWS, w.u);
-    if (ctx->bd == 1 ? (u == 4 || u == 8) : (u == 1 || u == 2)) w.u = u;
-  }
   memset(&w.ca, 0, sizeof(w.ca));
   w.ca.row_ptr = P<int64_t>(ctx->row_ptr);
   w.ca.col = P<int32_t>(ctx->col);
@@ -157,14 +147,38 @@ int rfo_rational_estimate(rfo_ctx *ctx, double mu, int64_t n_poles, const double
   w.ca.nb = ctx->nb;
   w.ca.plane = plane;
   w.ca.sp = sp;
-  w.ca.rows_per_wg = pl.rows_per_wg;
-  w.ca.n_rg = pl.n_rg;
-  w.ca.n_pt = sp / (64 * w.ppl);
+  w.u = 4;
+  int occ;
+  // 9x9: two column tiles per wave (half the instructions per column) where that leaves a wave for
+  // every compute unit, one below that and with an overlap, whose sums double the registers (16 poles,
+  // 128 probes, ms at one / two tiles: 13 atoms 98 / 102, 250 atoms 165 / 152, 1,000 atoms 320 / 278; with
+  // an overlap, 10 poles: 60 atoms and 60 probes 94 / 108, 300 atoms and 128 probes 196 / 201), and two
+  // tiles of a block row per workgroup (1,000 atoms: 278 against 289).
+  // 1x1: two probes per lane where the tiles allow: one tile of 128 probes reads the entries once
+  // per product (measured faster).
+  const int nt9 = !ctx->has_s && ctx->nb * (sp / 32) >= ctx->cus ? 2 : 1;
+  const int want = (int)tuned(ctx, RFO_TUNE_CPLX_PPL, ctx->bd == 9 ? nt9 : 2);
+  const int rows = (int)tuned(ctx, RFO_TUNE_CPLX_ROWS, 0);
+  if (ctx->bd == 9) {
+    w.ppl = want == 2 ? 2 : 1;
+    w.ca.tpw = rows == 1 ? 1 : 2;
+    w.ca.rows_per_wg = 4 / w.ca.tpw;  // one block row per row of waves
+    w.ca.n_rg = (int)((ctx->nb + w.ca.rows_per_wg - 1) / w.ca.rows_per_wg);
+    w.ca.n_pt = sp / (16 * w.ppl);
+    occ = rfo::cspmm9_blocks_per_cu(w.ppl, ctx->has_s);
+  } else {
+    w.ppl = sp % 128 == 0 && want == 2 ? 2 : 1;
+    if (rows == 8) w.u = 8;
+    w.ca.tpw = 1;
+    w.ca.rows_per_wg = pl.rows_per_wg;
+    w.ca.n_rg = pl.n_rg;
+    w.ca.n_pt = sp / (64 * w.ppl);
+    occ = rfo::cspmm_blocks_per_cu(w.ppl, w.u, ctx->has_s);
+  }
   {
-    const int occ = std::max(1, rfo::cspmm_blocks_per_cu(ctx->bd, w.ppl, w.u, ctx->has_s));
-    int64_t grid = (int64_t)ctx->cus * std::min(occ, 4);
+    int64_t grid = (int64_t)ctx->cus * std::min(std::max(1, occ), 4);
     grid = tuned(ctx, RFO_TUNE_CPLX_GRID, grid);
-    const int64_t units = (int64_t)w.ca.n_pt * w.ca.n_rg;
+    const int64_t units = (int64_t)(w.ca.n_pt / w.ca.tpw) * w.ca.n_rg;
     grid = std::min(grid, (units + 7) / 8 * 8);
     w.ca.grid = (int)std::max<int64_t>(8, grid / 8 * 8);
   }

@@ -43,12 +43,10 @@ __device__ __forceinline__ void flush_norm(double (&nrm)[PPL], double (*red)[64 
 // out = (H_hat - z) x on complex planes, with the column partials of |out_c|^2;
 // HS: out = H_hat x - z (S x) with the overlap S on the same pattern (H_hat then
 // maps H with S).  Same persistent XCD-banded schedule as the Chebyshev step
-// (Sched).  1x1 blocks: U neighbours per chunk, entries through the scalar cache;
-// 9x9 blocks: U blocks per chunk, their entries staged in the wave's LDS slice.
-template <int BD, int PPL, int U, bool HS>
+// (Sched), for 1x1 blocks (9x9: k_cspmm9.hip): U neighbours per chunk, entries through the
+// scalar cache.
+template <int PPL, int U, bool HS>
 __global__ __launch_bounds__(kWG) void k_cspmm(CspArgs a) {
-  constexpr int BB = BD * BD;
-  constexpr int NM = HS ? 2 : 1;  // matrices applied to x: H_hat (and S)
   const int wave = uniform(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int sp = a.sp;
@@ -59,7 +57,6 @@ __global__ __launch_bounds__(kWG) void k_cspmm(CspArgs a) {
   const double zr = a.zr, zi = a.zi;
   const bool nrm_on = a.part != nullptr;
   __shared__ double red[kWaves][64 * PPL];
-  __shared__ double hs[BD == 1 ? 1 : kWaves][BD == 1 ? 1 : NM * U * BB];
   double *prow = nrm_on ? a.part + (int64_t)blockIdx.x * sp : nullptr;
   if (nrm_on && wave == 0)
     for (int t = 0; t < a.n_pt; ++t)
@@ -82,137 +79,69 @@ __global__ __launch_bounds__(kWG) void k_cspmm(CspArgs a) {
     const int64_t r1 = min(a.nb, r0 + (int64_t)a.rows_per_wg);
     for (int64_t I = r0 + wave; I < r1; I += kWaves) {
       const int64_t beg = sld(a.row_ptr + I), end = sld(a.row_ptr + I + 1);
-      double sr[BD][PPL], si[BD][PPL];        // H_hat x
-      double tr[HS ? BD : 1][PPL], ti[HS ? BD : 1][PPL];  // S x
+      double sr[PPL], si[PPL];                      // H_hat x
+      double tr[HS ? PPL : 1], ti[HS ? PPL : 1];    // S x
 #pragma unroll
-      for (int i = 0; i < BD; ++i)
+      for (int q = 0; q < PPL; ++q) sr[q] = si[q] = 0.0;
 #pragma unroll
-        for (int q = 0; q < PPL; ++q) sr[i][q] = si[i][q] = 0.0;
+      for (int q = 0; q < (HS ? PPL : 1); ++q) tr[q] = ti[q] = 0.0;
+      for (int64_t nz0 = beg; nz0 < end; nz0 += U) {
+        int64_t J[U];
 #pragma unroll
-      for (int i = 0; i < (HS ? BD : 1); ++i)
-#pragma unroll
-        for (int q = 0; q < PPL; ++q) tr[i][q] = ti[i][q] = 0.0;
-      if constexpr (BD == 1) {
-        for (int64_t nz0 = beg; nz0 < end; nz0 += U) {
-          int64_t J[U];
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            // slots past the row's end re-read the row itself with weight zero
-            const int64_t Jc = sld(a.col + nz0 + u);
-            J[u] = nz0 + u < end ? Jc : I;
-          }
-          VecN<double, PPL> vr[U], vi[U];
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            vr[u] = ldv<double, PPL>(xr + J[u] * sp + c0);
-            vi[u] = ldv<double, PPL>(xi + J[u] * sp + c0);
-          }
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const double h = nz0 + u < end ? sld(a.hval + nz0 + u) : 0.0;
-#pragma unroll
-            for (int q = 0; q < PPL; ++q) {
-              sr[0][q] = fma(h, vr[u].v[q], sr[0][q]);
-              si[0][q] = fma(h, vi[u].v[q], si[0][q]);
-            }
-            if constexpr (HS) {
-              const double sv = nz0 + u < end ? sld(a.sval + nz0 + u) : 0.0;
-#pragma unroll
-              for (int q = 0; q < PPL; ++q) {
-                tr[0][q] = fma(sv, vr[u].v[q], tr[0][q]);
-                ti[0][q] = fma(sv, vi[u].v[q], ti[0][q]);
-              }
-            }
-          }
+        for (int u = 0; u < U; ++u) {
+          // slots past the row's end re-read the row itself with weight zero
+          const int64_t Jc = sld(a.col + nz0 + u);
+          J[u] = nz0 + u < end ? Jc : I;
         }
-      } else {
-        double *hw = hs[wave];
-        constexpr int CH = U * BB;               // H_hat entries per chunk (then as many of S)
-        constexpr int NH = (NM * CH + 63) / 64;
-        for (int64_t nz = beg; nz < end; nz += U) {
-          // U blocks per chunk; the value and column arrays carry kStepPad zero
-          // blocks past nnzb, and blocks past the row's end get no FMAs
-          double hv[NH];
+        VecN<double, PPL> vr[U], vi[U];
 #pragma unroll
-          for (int k = 0; k < NH; ++k) {
-            const int e = k * 64 + lane;
-            if (e < CH) hv[k] = a.hval[nz * BB + e];
-            else if (HS && e < NM * CH) hv[k] = a.sval[nz * BB + (e - CH)];
-          }
-          int64_t J[U];
-#pragma unroll
-          for (int u = 0; u < U; ++u) J[u] = sld(a.col + nz + u);
-          VecN<double, PPL> vr[U][BD], vi[U][BD];
-#pragma unroll
-          for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int j = 0; j < BD; ++j) {
-              vr[u][j] = ldv<double, PPL>(xr + (J[u] * BD + j) * sp + c0);
-              vi[u][j] = ldv<double, PPL>(xi + (J[u] * BD + j) * sp + c0);
-            }
-          __builtin_amdgcn_wave_barrier();
-#pragma unroll
-          for (int k = 0; k < NH; ++k) {
-            const int e = k * 64 + lane;
-            if (e < NM * CH) hw[e] = hv[k];
-          }
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-          __builtin_amdgcn_wave_barrier();
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            if (nz + u < end) {
-#pragma unroll
-              for (int i = 0; i < BD; ++i)
-#pragma unroll
-                for (int j = 0; j < BD; ++j) {
-                  const double h = hw[u * BB + i * BD + j];
-#pragma unroll
-                  for (int q = 0; q < PPL; ++q) {
-                    sr[i][q] = fma(h, vr[u][j].v[q], sr[i][q]);
-                    si[i][q] = fma(h, vi[u][j].v[q], si[i][q]);
-                  }
-                  if constexpr (HS) {
-                    const double sv = hw[CH + u * BB + i * BD + j];
-#pragma unroll
-                    for (int q = 0; q < PPL; ++q) {
-                      tr[i][q] = fma(sv, vr[u][j].v[q], tr[i][q]);
-                      ti[i][q] = fma(sv, vi[u][j].v[q], ti[i][q]);
-                    }
-                  }
-                }
-            }
-          }
+        for (int u = 0; u < U; ++u) {
+          vr[u] = ldv<double, PPL>(xr + J[u] * sp + c0);
+          vi[u] = ldv<double, PPL>(xi + J[u] * sp + c0);
         }
-      }
 #pragma unroll
-      for (int i = 0; i < BD; ++i) {
-        const int64_t off = (I * BD + i) * sp + c0;
-        VecN<double, PPL> ar, ai;
-        if constexpr (HS) {
+        for (int u = 0; u < U; ++u) {
+          const double h = nz0 + u < end ? sld(a.hval + nz0 + u) : 0.0;
 #pragma unroll
           for (int q = 0; q < PPL; ++q) {
-            ar.v[q] = tr[i][q];
-            ai.v[q] = ti[i][q];
+            sr[q] = fma(h, vr[u].v[q], sr[q]);
+            si[q] = fma(h, vi[u].v[q], si[q]);
           }
-        } else {
-          ar = ldv<double, PPL>(xr + off);
-          ai = ldv<double, PPL>(xi + off);
+          if constexpr (HS) {
+            const double sv = nz0 + u < end ? sld(a.sval + nz0 + u) : 0.0;
+#pragma unroll
+            for (int q = 0; q < PPL; ++q) {
+              tr[q] = fma(sv, vr[u].v[q], tr[q]);
+              ti[q] = fma(sv, vi[u].v[q], ti[q]);
+            }
+          }
         }
-        VecN<double, PPL> o_r, o_i;
+      }
+      const int64_t off = I * sp + c0;
+      VecN<double, PPL> ar, ai;
+      if constexpr (HS) {
 #pragma unroll
         for (int q = 0; q < PPL; ++q) {
-          // (h - z m) x with m x = (ar, ai) = x (S = I) or S x:
-          //   re = h xr - zr ar + zi ai,  im = h xi - zr ai - zi ar
-          const double vr = fma(zi, ai.v[q], fma(-zr, ar.v[q], sr[i][q]));
-          const double vi = fma(-zi, ar.v[q], fma(-zr, ai.v[q], si[i][q]));
-          o_r.v[q] = vr;
-          o_i.v[q] = vi;
-          if (nrm_on) nrm[q] = fma(vi, vi, fma(vr, vr, nrm[q]));
+          ar.v[q] = tr[q];
+          ai.v[q] = ti[q];
         }
-        stv<double, PPL>(orr + off, o_r);
-        stv<double, PPL>(oi + off, o_i);
+      } else {
+        ar = ldv<double, PPL>(xr + off);
+        ai = ldv<double, PPL>(xi + off);
       }
+      VecN<double, PPL> o_r, o_i;
+#pragma unroll
+      for (int q = 0; q < PPL; ++q) {
+        // (h - z m) x with m x = (ar, ai) = x (S = I) or S x:
+        //   re = h xr - zr ar + zi ai,  im = h xi - zr ai - zi ar
+        const double vr = fma(zi, ai.v[q], fma(-zr, ar.v[q], sr[q]));
+        const double vi = fma(-zi, ar.v[q], fma(-zr, ai.v[q], si[q]));
+        o_r.v[q] = vr;
+        o_i.v[q] = vi;
+        if (nrm_on) nrm[q] = fma(vi, vi, fma(vr, vr, nrm[q]));
+      }
+      stv<double, PPL>(orr + off, o_r);
+      stv<double, PPL>(oi + off, o_i);
     }
   }
   if (nrm_on && cur_pt >= 0) flush_norm<PPL>(nrm, red, wave, lane, prow, cur_pt);
@@ -221,21 +150,14 @@ __global__ __launch_bounds__(kWG) void k_cspmm(CspArgs a) {
 namespace {
 
 template <bool HS>
-const void *select_cspmm_t(int bd, int ppl, int u) {
-  if (bd == 1) {
-    if (u == 8) return ppl == 2 ? (const void *)k_cspmm<1, 2, 8, HS> : (const void *)k_cspmm<1, 1, 8, HS>;
-    return ppl == 2 ? (const void *)k_cspmm<1, 2, 4, HS> : (const void *)k_cspmm<1, 1, 4, HS>;
-  }
-  if (bd == 9) {
-    if (u == 2) return ppl == 2 ? (const void *)k_cspmm<9, 2, 2, HS> : (const void *)k_cspmm<9, 1, 2, HS>;
-    return ppl == 2 ? (const void *)k_cspmm<9, 2, 1, HS> : (const void *)k_cspmm<9, 1, 1, HS>;
-  }
-  return nullptr;
+const void *select_cspmm_t(int ppl, int u) {
+  if (u == 8) return ppl == 2 ? (const void *)k_cspmm<2, 8, HS> : (const void *)k_cspmm<1, 8, HS>;
+  return ppl == 2 ? (const void *)k_cspmm<2, 4, HS> : (const void *)k_cspmm<1, 4, HS>;
 }
 
-// u: neighbours per chunk (1x1: 4 or 8; 9x9: blocks per chunk, 1 or 2); hs: with S
-const void *select_cspmm(int bd, int ppl, int u, bool hs) {
-  return hs ? select_cspmm_t<true>(bd, ppl, u) : select_cspmm_t<false>(bd, ppl, u);
+// u: neighbours per chunk (4 or 8); hs: with S
+const void *select_cspmm(int ppl, int u, bool hs) {
+  return hs ? select_cspmm_t<true>(ppl, u) : select_cspmm_t<false>(ppl, u);
 }
 
 // rows [lo, hi) of workgroup b when n rows are split over gridDim.x workgroups
@@ -276,17 +198,16 @@ struct ColLanes {
 
 }  // namespace
 
-int cspmm_blocks_per_cu(int bd, int ppl, int u, bool hs) {
-  const void *f = select_cspmm(bd, ppl, u, hs);
-  if (!f) return 0;
+int cspmm_blocks_per_cu(int ppl, int u, bool hs) {
+  const void *f = select_cspmm(ppl, u, hs);
   int nb = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, kWG, 0) != hipSuccess) return 0;
   return nb;
 }
 
-hipError_t launch_cspmm(int bd, int ppl, int u, const CspArgs &a, hipStream_t s) {
-  const void *f = select_cspmm(bd, ppl, u, a.sval != nullptr);
-  if (!f || a.sp % (64 * ppl) != 0 || a.grid % 8 != 0 || a.grid <= 0) return hipErrorInvalidValue;
+hipError_t launch_cspmm(int ppl, int u, const CspArgs &a, hipStream_t s) {
+  const void *f = select_cspmm(ppl, u, a.sval != nullptr);
+  if (a.sp % (64 * ppl) != 0 || a.grid % 8 != 0 || a.grid <= 0) return hipErrorInvalidValue;
   CspArgs args = a;
   void *kargs[] = {&args};
   return hipLaunchKernel(f, dim3(a.grid), dim3(kWG), kargs, 0, s);

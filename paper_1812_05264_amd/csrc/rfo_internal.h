@@ -272,12 +272,16 @@ struct CspArgs {
   int64_t plane;           // n * sp
   int sp;
   int rows_per_wg;
-  int n_rg, n_pt;          // n_pt probe tiles of 64 * ppl
+  int n_rg, n_pt;          // n_pt probe tiles of 64 * ppl (9x9: 16 * nt)
+  int tpw;                 // 9x9: tiles of one block row per workgroup (1 or 2)
   int grid;                // multiple of 8
 };
-// u: neighbours per chunk (1x1: 4 or 8; 9x9: blocks per chunk, 1 or 2)
-hipError_t launch_cspmm(int bd, int ppl, int u, const CspArgs &a, hipStream_t s);
-int cspmm_blocks_per_cu(int bd, int ppl, int u, bool hs);
+// 1x1 blocks; ppl: probes per lane (1, 2), u: neighbours per chunk (4 or 8)
+hipError_t launch_cspmm(int ppl, int u, const CspArgs &a, hipStream_t s);
+int cspmm_blocks_per_cu(int ppl, int u, bool hs);
+// 9x9 blocks; nt: probe tiles of 16 columns per wave (1, 2)
+hipError_t launch_cspmm9(int nt, const CspArgs &a, hipStream_t s);
+int cspmm9_blocks_per_cu(int nt, bool hs);
 // dre = scale * y (probes), dim = 0 when non-null
 hipError_t launch_cx_fill(const uint64_t *sgn, const double *rden, int64_t n, int sp, double scale,
                           double *dre, double *dim, hipStream_t s);
