@@ -464,7 +464,7 @@ struct Checkpoints {
 
 inline int ensure_cg(rfo_ctx *ctx) {
   TRY(ensure(ctx, ctx->cg_part, (size_t)rfo::cg_nparts(ctx->n) * ctx->sp * sizeof(double)));
-  TRY(ensure(ctx, ctx->cg_sc, ((size_t)6 * ctx->sp + 1) * sizeof(double)));
+  TRY(ensure(ctx, ctx->cg_sc, ((size_t)7 * ctx->sp + 1) * sizeof(double)));
   if (!ctx->cg_res_h) HIPCHK(hipHostMalloc((void **)&ctx->cg_res_h, sizeof(double), 0));
   return RFO_OK;
 }
@@ -476,13 +476,13 @@ inline int cg_solve(rfo_ctx *ctx, const Plan &pl, DevBuf &bufs, const void *y, v
   const int sp = ctx->sp;
   // the kernels below write these buffers: never launch them unallocated or too small
   if (!ctx->cg_res_h || ctx->cg_part.bytes < (size_t)rfo::cg_nparts(n) * sp * sizeof(double) ||
-      ctx->cg_sc.bytes < ((size_t)6 * sp + 1) * sizeof(double) || bufs.bytes < 6 * pl.slot_bytes)
+      ctx->cg_sc.bytes < ((size_t)7 * sp + 1) * sizeof(double) || bufs.bytes < 6 * pl.slot_bytes)
     return fail(ctx, RFO_E_STATE, "internal: conjugate-gradient buffers not allocated");
   double *r = reinterpret_cast<double *>(vec_at(ctx, pl, bufs, 3));
   double *pv = reinterpret_cast<double *>(vec_at(ctx, pl, bufs, 4));
   double *q = reinterpret_cast<double *>(vec_at(ctx, pl, bufs, 5));
   double *part = P<double>(ctx->cg_part), *sc = P<double>(ctx->cg_sc);
-  double *res_d = sc + 6 * sp;
+  double *res_d = sc + 7 * sp;
   // the product's column partials of p . q (the step kernel's moment partials with p
   // as the probe block): one pass over p and q fewer per iteration
   TRY(ensure(ctx, ctx->cg_spart, (size_t)pl.grid * sp * sizeof(double)));
@@ -504,9 +504,8 @@ inline int cg_solve(rfo_ctx *ctx, const Plan &pl, DevBuf &bufs, const void *y, v
   const int max_it = 2000;
   for (int it = 1; it <= max_it; ++it) {
     HIPCHK(launch_any_step(ctx, pl, sa));
-    HIPCHK(rfo::launch_cg_alpha(spart, pl.grid, sp, sc, res_d, ctx->stream));
-    HIPCHK(rfo::launch_cg_update(static_cast<double *>(t), r, pv, q, n, sp, part, sc, res_d,
-                                 ctx->stream));
+    HIPCHK(rfo::launch_cg_update(static_cast<double *>(t), r, pv, q, spart, pl.grid, it, n, sp, part, sc,
+                                 res_d, ctx->stream));
     ++ctx->cg_iters;
     // the host looks at the residual every 4th iteration: up to three extra
     // iterations only shrink it further (a column whose residual is exactly zero

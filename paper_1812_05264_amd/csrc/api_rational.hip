@@ -47,8 +47,7 @@ int cgls_solve(rfo_ctx *ctx, CxWork &w, double zr, double zi, double tol, int64_
   const uint64_t *sgn = rhs ? nullptr : ctx->signs ? P<uint64_t>(ctx->sgn) : nullptr;
   const double *rden = rhs ? rhs : ctx->signs ? nullptr : P<double>(ctx->rden);
   double *sc = w.sc;
-  double *yy = sc, *ssn = sc + 3 * sp, *rr = sc + 4 * sp, *al = sc + 5 * sp, *be = sc + 6 * sp,
-         *res_d = sc + 7 * sp;
+  double *yy = sc, *ssn = sc + 3 * sp, *rr = sc + 4 * sp, *res_d = sc + 8 * sp;
   const double tol2 = tol * tol;
   auto converged = [&](bool &done) -> int {
     HIPCHK(hipMemcpyAsync(ctx->rat_res_h, res_d, sizeof(double), hipMemcpyDeviceToHost,
@@ -63,12 +62,11 @@ int cgls_solve(rfo_ctx *ctx, CxWork &w, double zr, double zi, double tol, int64_
   if (!first) TRY(cspmm(ctx, w, w.x, w.q, zr, zi, nullptr));
   HIPCHK(rfo::launch_cx_resid(sgn, rden, first ? nullptr : w.q, w.r, n, sp, w.part, w.part2,
                               ctx->stream));
-  HIPCHK(rfo::launch_colreduce(w.part, G, sp, rr, ctx->stream));
-  HIPCHK(rfo::launch_colreduce(w.part2, G, sp, yy, ctx->stream));
+  HIPCHK(rfo::launch_colreduce(w.part, G, sp, rr, ctx->stream, w.part2, G, yy));
   // s = A^H r (A^H = H_hat - conj(z)), p = s
   TRY(cspmm(ctx, w, w.r, w.s, zr, -zi, w.part));
   HIPCHK(rfo::launch_colreduce(w.part, grid, sp, ssn, ctx->stream));
-  HIPCHK(rfo::launch_cgls_scalars(sc, sp, 0, res_d, ctx->stream));
+  HIPCHK(rfo::launch_cgls_start(sc, sp, res_d, ctx->stream));
   HIPCHK(hipMemcpyAsync(w.p, w.s, (size_t)2 * n * sp * sizeof(double), hipMemcpyDeviceToDevice,
                         ctx->stream));
   bool done = false;
@@ -80,11 +78,10 @@ int cgls_solve(rfo_ctx *ctx, CxWork &w, double zr, double zi, double tol, int64_
   }
   for (int64_t it = 1; it <= max_iter; ++it) {
     TRY(cspmm(ctx, w, w.p, w.q, zr, zi, w.part));  // q = A p
-    HIPCHK(rfo::launch_cgls_reduce(w.part, grid, nullptr, 0, sp, sc, 1, res_d, ctx->stream));
-    HIPCHK(rfo::launch_cx_update(w.r, w.q, al, n, sp, w.part2, ctx->stream));  // |r|^2 partials
+    HIPCHK(rfo::launch_cgls_update(w.r, w.q, w.part, grid, sc, it, n, sp, w.part2, res_d, ctx->stream));
     TRY(cspmm(ctx, w, w.r, w.s, zr, -zi, w.part));  // s = A^H r
-    HIPCHK(rfo::launch_cgls_reduce(w.part, grid, w.part2, G, sp, sc, 2, res_d, ctx->stream));
-    HIPCHK(rfo::launch_cx_dir(w.s, w.p, w.x, al, be, n, sp, ctx->stream));  // x += alpha p, new p
+    // x += alpha p, new p
+    HIPCHK(rfo::launch_cgls_dir(w.s, w.p, w.x, w.part, grid, w.part2, sc, it, n, sp, res_d, ctx->stream));
     ++ctx->cgls_iters;
     if (it % 4 != 0 && it != max_iter) continue;
     TRY(converged(done));
@@ -192,7 +189,7 @@ int rfo_rational_estimate(rfo_ctx *ctx, double mu, int64_t n_poles, const double
     TRY(ensure_cg(ctx));
   }
   TRY(ensure(ctx, ctx->rat_part, (size_t)2 * w.nparts * sp * sizeof(double)));
-  TRY(ensure(ctx, ctx->rat_sc, ((size_t)7 * sp + 1) * sizeof(double)));
+  TRY(ensure(ctx, ctx->rat_sc, ((size_t)8 * sp + 1) * sizeof(double)));
   TRY(ensure(ctx, ctx->rat_rho, ((size_t)2 * n_poles + 2) * sp * sizeof(double)));
   TRY(ensure(ctx, ctx->rat_coef, (size_t)6 * n_poles * sizeof(double)));
   TRY(ensure(ctx, ctx->small, 64 * sizeof(double)));
@@ -340,9 +337,8 @@ int rfo_rational_estimate(rfo_ctx *ctx, double mu, int64_t n_poles, const double
     const double wr = 2.0 * res_f[2 * k] / c, wi = 2.0 * res_f[2 * k + 1] / c;
     HIPCHK(rfo::launch_cx_pdot(sgn, rden, Sr, w.x, w.x + plane, n, sp, dens ? w.acc : nullptr, wr, wi,
                                w.part, w.part2, ctx->stream));
-    HIPCHK(rfo::launch_colreduce(w.part, rfo::cg_nparts(n), sp, rho + (size_t)2 * k * sp, ctx->stream));
-    HIPCHK(rfo::launch_colreduce(w.part2, rfo::cg_nparts(n), sp, rho + (size_t)(2 * k + 1) * sp,
-                                 ctx->stream));
+    HIPCHK(rfo::launch_colreduce(w.part, rfo::cg_nparts(n), sp, rho + (size_t)2 * k * sp, ctx->stream,
+                                 w.part2, rfo::cg_nparts(n), rho + (size_t)(2 * k + 1) * sp));
     if (grad_s) {
       // h_k c = x2 = (H_hat - z_hat S)^{-1} S r; with g_k = x1 / c, h_k = x2 / c, z_k the pole:
       //   dF/dH += -2 Re[tau_k h_k g_k^T],  dF/dS += 2 Re[tau_k (r g_k^T + z_k h_k g_k^T)],

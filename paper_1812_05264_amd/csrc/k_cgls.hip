@@ -7,8 +7,8 @@
 // Chebyshev vectors, so the real H_hat multiplies both planes with the same
 // gathers and block values.  Column sums (norms, inner products with the
 // probes) are written as per-workgroup partials and reduced in a fixed order
-// (launch_colreduce, or k_cgls_reduce with the CGLS scalars), so every scalar is
-// bitwise reproducible.
+// (launch_colreduce, or the vector kernel that uses them: colsum.h), so every scalar
+// is bitwise reproducible.
 #include "colsum.h"
 #include "device_util.h"
 #include "rfo_internal.h"
@@ -255,44 +255,79 @@ __global__ __launch_bounds__(kWG) void k_cx_resid(const uint64_t *sgn, const dou
   }
 }
 
-// r -= alpha_c q (complex planes, real alpha); partials of |r_c|^2
-__global__ __launch_bounds__(kWG) void k_cx_update(double *__restrict__ r,
-                                                   const double *__restrict__ q,
-                                                   const double *__restrict__ alpha, int64_t n,
-                                                   int sp, int64_t plane,
-                                                   double *__restrict__ part) {
-  int64_t lo, hi;
-  row_range(n, lo, hi);
-  const ColLanes cl(sp);
-  __shared__ double red[kWG];
-  for (int c = cl.c0; c < sp; c += cl.cstep) {
-    const double al = alpha[c];
-    double rr = 0.0;
-    for (int64_t i = lo + cl.lr; i < hi; i += cl.nl) {
-      const int64_t e = i * sp + c;
-      const double a = fma(-al, q[e], r[e]);
-      const double b = fma(-al, q[plane + e], r[plane + e]);
-      r[e] = a;
-      r[plane + e] = b;
-      rr = fma(b, b, fma(a, a, rr));
-    }
-    cl.finish(rr, c, sp, red, part + (int64_t)blockIdx.x * sp);
+// One CGLS iteration's vector kernels on complex planes, real scalars sc = [yy | gam0 | qq | ssn | rr |
+// alpha | beta | gam1] of sp each (gam of iteration it in gam{(it - 1) & 1}, so that no workgroup
+// reads what another has replaced).
+// k_cgls_update, after q = A p: qq = sums of pa [na][sp], alpha = gam / qq, r -= alpha q, part =
+// [shares][sp] partials of |r|^2; *resmax = 0 for k_cgls_dir.
+template <int C>
+__global__ __launch_bounds__(kSlabThreads) void k_cgls_update(double *__restrict__ r,
+                                                              const double *__restrict__ q,
+                                                              const double *__restrict__ pa, int na,
+                                                              double *__restrict__ sc, int odd, int64_t n, int sp,
+                                                              int64_t plane, double *__restrict__ part, int shares,
+                                                              double *__restrict__ resmax) {
+  __shared__ double red[2][kSlabWaves][C];
+  const Slab<C> sl(n, sp, shares);
+  const int c = sl.c;
+  const double qq = slab_sum<C>(pa, na, sp, c, red[0]);
+  const double gam = sc[(odd ? 7 : 1) * sp + c];
+  const double al = (gam > 0.0 && qq > 0.0) ? gam / qq : 0.0;
+  if (sl.first && threadIdx.x < C) {
+    sc[2 * sp + c] = qq;
+    sc[5 * sp + c] = al;
+    if (c == 0) *resmax = 0.0;
   }
+  double rr = 0.0;
+#pragma unroll 4
+  for (int64_t i = sl.lo; i < sl.hi; i += sl.step) {
+    const int64_t e = i * sp + c;
+    const double a = fma(-al, q[e], r[e]);
+    const double b = fma(-al, q[plane + e], r[plane + e]);
+    r[e] = a;
+    r[plane + e] = b;
+    rr = fma(b, b, fma(a, a, rr));
+  }
+  rr = slab_total<C>(rr, red[1]);
+  if (threadIdx.x < C) part[(int64_t)sl.share * sp + c] = rr;
 }
 
-// x += alpha_c p, then p = s + beta_c p (both planes): the step of the solution
-// along the direction of this iteration, and the next direction
-__global__ __launch_bounds__(kWG) void k_cx_dir(const double *__restrict__ sv, double *__restrict__ p,
-                                                double *__restrict__ x,
-                                                const double *__restrict__ alpha,
-                                                const double *__restrict__ beta, int64_t n2,
-                                                int sp) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n2;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int c = (int)(e % sp);
+// k_cgls_dir, after s = A^H r: ssn = sums of pa [na][sp], rr = sums of pb [nb][sp], beta = ssn / gam, the
+// next gam = ssn; x += alpha p, p = s + beta p; *resmax = max_c rr / yy over columns with yy > 0 (an
+// integer max on the bit patterns of non-negative doubles), +inf for a non-finite rr or ssn.
+// The planes are taken as 2 n rows.
+template <int C>
+__global__ __launch_bounds__(kSlabThreads) void k_cgls_dir(const double *__restrict__ sv, double *__restrict__ p,
+                                                           double *__restrict__ x, const double *__restrict__ pa,
+                                                           int na, const double *__restrict__ pb, int nb,
+                                                           double *__restrict__ sc, int odd, int64_t n2, int sp,
+                                                           double *__restrict__ resmax) {
+  __shared__ double red[2][kSlabWaves][C];
+  const Writer<C> wr(n2, sp);
+  const int c = wr.c;
+  const double ssn = slab_sum<C>(pa, na, sp, c, red[0]);
+  const double gam = sc[(odd ? 7 : 1) * sp + c], al = sc[5 * sp + c];
+  const double be = gam > 0.0 ? ssn / gam : 0.0;
+  if (wr.lead) {  // the whole workgroup: slab_sum has a barrier
+    const double rr = slab_sum<C>(pb, nb, sp, c, red[1]);
+    if (wr.first) {
+      const double yy = sc[c];
+      sc[3 * sp + c] = ssn;
+      sc[4 * sp + c] = rr;
+      sc[6 * sp + c] = be;
+      sc[(odd ? 1 : 7) * sp + c] = ssn;
+      double m = -1.0;
+      if (yy > 0.0) m = rr / yy;
+      if (!isfinite(rr) || !isfinite(ssn)) m = HUGE_VAL;
+      if (m >= 0.0)
+        atomicMax(reinterpret_cast<unsigned long long *>(resmax), (unsigned long long)__double_as_longlong(m));
+    }
+  }
+#pragma unroll 4
+  for (int64_t e = wr.e; e < wr.end; e += wr.step) {
     const double pv = p[e];
-    x[e] = fma(alpha[c], pv, x[e]);
-    p[e] = fma(beta[c], pv, sv[e]);
+    x[e] = fma(al, pv, x[e]);
+    p[e] = fma(be, pv, sv[e]);
   }
 }
 
@@ -323,26 +358,17 @@ __global__ __launch_bounds__(kWG) void k_cx_pdot(const uint64_t *sgn, const doub
   }
 }
 
-// Per-column CGLS scalars (one workgroup), sc = [yy | gam | qq | ssn | rr | alpha | beta]:
-// mode 0 (start): gam = ssn;  mode 1: alpha = gam / qq;  mode 2: beta = ssn / gam,
-// gam = ssn.  Modes 0 and 2 write *resmax = max_c rr / yy over columns with yy > 0.
-__global__ __launch_bounds__(kWG) void k_cgls_scalars(double *__restrict__ sc, int sp, int mode,
-                                                      double *__restrict__ resmax) {
-  double *yy = sc, *gam = sc + sp, *qq = sc + 2 * sp, *ssn = sc + 3 * sp, *rr = sc + 4 * sp,
-         *al = sc + 5 * sp, *be = sc + 6 * sp;
+// Start of a solve (one workgroup) on sc: gam0 = ssn, *resmax = max_c rr / yy over columns with yy > 0.
+__global__ __launch_bounds__(kWG) void k_cgls_start(double *__restrict__ sc, int sp, double *__restrict__ resmax) {
+  const double *yy = sc, *ssn = sc + 3 * sp, *rr = sc + 4 * sp;
+  double *gam = sc + sp;
   double m = 0.0;
   for (int c = threadIdx.x; c < sp; c += blockDim.x) {
-    if (mode == 1) {
-      al[c] = (gam[c] > 0.0 && qq[c] > 0.0) ? gam[c] / qq[c] : 0.0;
-    } else {
-      if (mode == 2) be[c] = gam[c] > 0.0 ? ssn[c] / gam[c] : 0.0;
-      gam[c] = ssn[c];
-      if (yy[c] > 0.0) m = fmax(m, rr[c] / yy[c]);
-      // a non-finite residual must reach the host check (fmax drops NaN)
-      if (!isfinite(rr[c]) || !isfinite(ssn[c])) m = HUGE_VAL;
-    }
+    gam[c] = ssn[c];
+    if (yy[c] > 0.0) m = fmax(m, rr[c] / yy[c]);
+    // a non-finite residual must reach the host check (fmax drops NaN)
+    if (!isfinite(rr[c]) || !isfinite(ssn[c])) m = HUGE_VAL;
   }
-  if (mode == 1) return;
   m = wave_max(m);
   __shared__ double red[kWaves];
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
@@ -352,43 +378,6 @@ __global__ __launch_bounds__(kWG) void k_cgls_scalars(double *__restrict__ sc, i
     for (int w = 1; w < kWaves; ++w) t = fmax(t, red[w]);
     *resmax = t;
   }
-}
-
-// One CGLS half-iteration's column sums (colsum's fixed order, as launch_colreduce) and
-// scalars in one kernel, on sc = [yy | gam | qq | ssn | rr | alpha | beta]:
-//   mode 1: qq = sums of pa [na][sp]; alpha = gam / qq; *resmax = 0 for mode 2.
-//   mode 2: ssn = sums of pa [na][sp], rr = sums of pb [nb][sp]; beta = ssn / gam,
-//           gam = ssn, *resmax = max_c rr / yy over columns with yy > 0 (an integer max
-//           on the bit patterns of non-negative doubles), +inf for a non-finite rr or ssn.
-__global__ __launch_bounds__(64 * kColWaves) void k_cgls_reduce(const double *__restrict__ pa, int na,
-                                                                const double *__restrict__ pb, int nb,
-                                                                int sp, double *__restrict__ sc,
-                                                                int mode,
-                                                                double *__restrict__ resmax) {
-  __shared__ double red_a[kColPh][kColCols], red_b[kColPh][kColCols];
-  int c;
-  const double va = colsum(pa, na, sp, red_a, c);
-  const double vb = mode == 2 ? colsum(pb, nb, sp, red_b, c) : 0.0;
-  if (threadIdx.x >= kColCols) return;
-  double *yy = sc, *gam = sc + sp, *qq = sc + 2 * sp, *ssn = sc + 3 * sp, *rr = sc + 4 * sp,
-         *al = sc + 5 * sp, *be = sc + 6 * sp;
-  if (mode == 1 && blockIdx.x == 0 && threadIdx.x == 0) *resmax = 0.0;
-  if (c >= sp) return;
-  if (mode == 1) {
-    qq[c] = va;
-    al[c] = (gam[c] > 0.0 && va > 0.0) ? gam[c] / va : 0.0;
-    return;
-  }
-  ssn[c] = va;
-  rr[c] = vb;
-  be[c] = gam[c] > 0.0 ? va / gam[c] : 0.0;
-  gam[c] = va;
-  double m = -1.0;
-  if (yy[c] > 0.0) m = vb / yy[c];
-  if (!isfinite(vb) || !isfinite(va)) m = HUGE_VAL;
-  if (m >= 0.0)
-    atomicMax(reinterpret_cast<unsigned long long *>(resmax),
-              (unsigned long long)__double_as_longlong(m));
 }
 
 // N, E, F of the rational estimate (one workgroup, fixed order):
@@ -454,17 +443,46 @@ hipError_t launch_cx_resid(const uint64_t *sgn, const double *rden, const double
   return hipGetLastError();
 }
 
-hipError_t launch_cx_update(double *r, const double *q, const double *alpha, int64_t n, int sp,
-                            double *part, hipStream_t s) {
-  hipLaunchKernelGGL(k_cx_update, dim3(cg_nparts(n)), dim3(kWG), 0, s, r, q, alpha, n, sp, n * sp,
-                     part);
+template <int C>
+static void launch_cgls_update_t(double *r, const double *q, const double *pa, int na, double *sc, int64_t it,
+                                 int64_t n, int sp, double *part, double *resmax, hipStream_t s) {
+  const int shares = slab_shares<C>(n, sp);
+  hipLaunchKernelGGL((k_cgls_update<C>), dim3(sp / C * shares), dim3(kSlabThreads), 0, s, r, q, pa, na, sc,
+                     (int)((it - 1) & 1), n, sp, n * sp, part, shares, resmax);
+}
+
+hipError_t launch_cgls_update(double *r, const double *q, const double *pa, int na, double *sc, int64_t it,
+                              int64_t n, int sp, double *part, double *resmax, hipStream_t s) {
+  if (sp <= 0 || sp % 64 != 0 || n <= 0) return hipErrorInvalidValue;
+  if (slab_wide(n, sp)) {
+    const hipError_t e = launch_colreduce(pa, na, sp, sc + 2 * sp, s);  // |q|^2 itself
+    if (e != hipSuccess) return e;
+    launch_cgls_update_t<64>(r, q, sc + 2 * sp, 1, sc, it, n, sp, part, resmax, s);
+  } else {
+    launch_cgls_update_t<16>(r, q, pa, na, sc, it, n, sp, part, resmax, s);
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_cx_dir(const double *sv, double *p, double *x, const double *alpha,
-                         const double *beta, int64_t n, int sp, hipStream_t s) {
-  hipLaunchKernelGGL(k_cx_dir, dim3(ew_blocks(2 * n * sp)), dim3(kWG), 0, s, sv, p, x, alpha, beta,
-                     2 * n * sp, sp);
+template <int C>
+static void launch_cgls_dir_t(const double *sv, double *p, double *x, const double *pa, int na, const double *pb,
+                              int nb, double *sc, int64_t it, int64_t n, int sp, double *resmax, hipStream_t s) {
+  hipLaunchKernelGGL((k_cgls_dir<C>), dim3(Writer<C>::grid(n, 2 * n, sp)), dim3(kSlabThreads), 0, s, sv, p, x, pa, na,
+                     pb, nb, sc, (int)((it - 1) & 1), 2 * n, sp, resmax);
+}
+
+hipError_t launch_cgls_dir(const double *sv, double *p, double *x, const double *pa, int na, const double *pb,
+                           double *sc, int64_t it, int64_t n, int sp, double *resmax, hipStream_t s) {
+  if (sp <= 0 || sp % 64 != 0 || n <= 0) return hipErrorInvalidValue;
+  if (!slab_wide(n, sp)) {
+    launch_cgls_dir_t<16>(sv, p, x, pa, na, pb, slab_shares<16>(n, sp), sc, it, n, sp, resmax, s);
+    return hipGetLastError();
+  }
+  // |s|^2 and |r|^2 themselves
+  const hipError_t e =
+      launch_colreduce(pa, na, sp, sc + 3 * sp, s, pb, slab_shares<64>(n, sp), sc + 4 * sp);
+  if (e != hipSuccess) return e;
+  launch_cgls_dir_t<64>(sv, p, x, sc + 3 * sp, 1, sc + 4 * sp, 1, sc, it, n, sp, resmax, s);
   return hipGetLastError();
 }
 
@@ -490,16 +508,8 @@ hipError_t launch_cx_scale(const double *src, double *dst, int64_t n, double alp
   return hipGetLastError();
 }
 
-hipError_t launch_cgls_scalars(double *sc, int sp, int mode, double *resmax, hipStream_t s) {
-  hipLaunchKernelGGL(k_cgls_scalars, dim3(1), dim3(kWG), 0, s, sc, sp, mode, resmax);
-  return hipGetLastError();
-}
-
-hipError_t launch_cgls_reduce(const double *pa, int na, const double *pb, int nb, int sp, double *sc,
-                              int mode, double *resmax, hipStream_t s) {
-  if (sp <= 0 || (mode != 1 && mode != 2) || (mode == 2 && !pb)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_cgls_reduce, dim3((sp + kColCols - 1) / kColCols), dim3(64 * kColWaves), 0, s,
-                     pa, na, pb, nb, sp, sc, mode, resmax);
+hipError_t launch_cgls_start(double *sc, int sp, double *resmax, hipStream_t s) {
+  hipLaunchKernelGGL(k_cgls_start, dim3(1), dim3(kWG), 0, s, sc, sp, resmax);
   return hipGetLastError();
 }
 

@@ -222,7 +222,7 @@ hipError_t launch_forces(const int64_t *row_ptr, const int64_t *tpos,
 
 // ---------------------------------------------------------------------------
 // Nonorthogonal basis: H_hat with S, and conjugate gradients for S t = y per
-// probe column.  sc holds [yy | rr | pq | rrn | alpha | beta] (sp each), part
+// probe column.  sc holds [yy | rr0 | pq | rrn | alpha | beta | rr1] (sp each), part
 // [cg_nparts(n)][sp] column partials, resmax the largest rrn / yy after an update.
 // sp must be a positive multiple of 64 (hipErrorInvalidValue otherwise).
 // ---------------------------------------------------------------------------
@@ -233,23 +233,23 @@ int cg_nparts(int64_t n);
 // t = 0, r = p = y, yy = rr = |y_c|^2
 hipError_t launch_cg_init(const double *y, double *t, double *r, double *p, int64_t n, int sp,
                           double *part, double *sc, hipStream_t s);
-// alpha_c = rr_c / (p_c . q_c) from the column partials of p . q that the product
-// q = S p left in part [nparts][sp] (its moment partials with p as the probe block);
-// sets *resmax = 0 for the update that follows
-hipError_t launch_cg_alpha(const double *part, int nparts, int sp, double *sc, double *resmax,
-                           hipStream_t s);
+// iteration it (1, 2, ...) after q = S p, whose product left the column partials of p . q in
+// spart [ns][sp] (its moment partials with p as the probe block): alpha = rr / (p . q),
 // t += alpha p, r -= alpha q, beta = |r|^2 / rr, rr = |r|^2, p = r + beta p, *resmax
-hipError_t launch_cg_update(double *t, double *r, double *p, const double *q, int64_t n, int sp,
-                            double *part, double *sc, double *resmax, hipStream_t s);
+hipError_t launch_cg_update(double *t, double *r, double *p, const double *q, const double *spart, int ns,
+                            int64_t it, int64_t n, int sp, double *part, double *sc, double *resmax,
+                            hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // Rational expansion with S = I: CGLS for (H_hat - z) x = y per probe column on
 // complex vectors stored as two real [n][sp] planes (re, then im, `plane`
 // elements apart).  Column partials are [nparts][sp]; launch_colreduce sums
-// them in a fixed order.  CGLS scalars sc = [yy | gam | qq | ssn | rr | alpha |
-// beta] (sp each).
+// them in a fixed order.  CGLS scalars sc = [yy | gam0 | qq | ssn | rr | alpha |
+// beta | gam1] (sp each).
 // ---------------------------------------------------------------------------
-hipError_t launch_colreduce(const double *part, int nparts, int sp, double *out, hipStream_t s);
+// (part2: another such sum in the same launch)
+hipError_t launch_colreduce(const double *part, int nparts, int sp, double *out, hipStream_t s,
+                            const double *part2 = nullptr, int nparts2 = 0, double *out2 = nullptr);
 // out = ca A + cb B + cc C + cr r over n rows of sp FP64 columns (null operands add nothing;
 // r from sgn or rden as in the step kernels)
 hipError_t launch_combine(double *out, double ca, const double *A, double cb, const double *B, double cc,
@@ -288,12 +288,13 @@ hipError_t launch_cx_fill(const uint64_t *sgn, const double *rden, int64_t n, in
 // r = y - q (q == nullptr: r = y); partials |r_c|^2 and |y_c|^2 ([cg_nparts(n)][sp] each)
 hipError_t launch_cx_resid(const uint64_t *sgn, const double *rden, const double *q, double *r,
                            int64_t n, int sp, double *part_rr, double *part_yy, hipStream_t s);
-// r -= alpha_c q; partials |r_c|^2
-hipError_t launch_cx_update(double *r, const double *q, const double *alpha, int64_t n, int sp,
-                            double *part, hipStream_t s);
-// x += alpha_c p, then p = s + beta_c p
-hipError_t launch_cx_dir(const double *sv, double *p, double *x, const double *alpha,
-                         const double *beta, int64_t n, int sp, hipStream_t s);
+// iteration it (1, 2, ...) of a solve.  After q = A p with its partials pa [na][sp]: alpha, r -= alpha q,
+// partials |r_c|^2 (at most cg_nparts(n) rows of part)
+hipError_t launch_cgls_update(double *r, const double *q, const double *pa, int na, double *sc, int64_t it,
+                              int64_t n, int sp, double *part, double *resmax, hipStream_t s);
+// after s = A^H r with its partials pa [na][sp], pb the update's: beta, x += alpha p, p = s + beta p, *resmax
+hipError_t launch_cgls_dir(const double *sv, double *p, double *x, const double *pa, int na, const double *pb,
+                           double *sc, int64_t it, int64_t n, int sp, double *resmax, hipStream_t s);
 // partials y_c . a_c, y_c . b_c with y the probes (yd == nullptr) or the plane yd;
 // acc += wr a - wi b when acc != nullptr
 hipError_t launch_cx_pdot(const uint64_t *sgn, const double *rden, const double *yd, const double *a,
@@ -301,14 +302,8 @@ hipError_t launch_cx_pdot(const uint64_t *sgn, const double *rden, const double 
                           double *part_a, double *part_b, hipStream_t s);
 // dst = alpha * src (n elements)
 hipError_t launch_cx_scale(const double *src, double *dst, int64_t n, double alpha, hipStream_t s);
-// mode 0: gam = ssn, *resmax;  1: alpha = gam / qq;  2: beta = ssn / gam, gam = ssn, *resmax
-hipError_t launch_cgls_scalars(double *sc, int sp, int mode, double *resmax, hipStream_t s);
-// the column sums and scalars of one half-iteration in one kernel: mode 1 reduces pa
-// [na][sp] into qq and forms alpha (and zeroes *resmax); mode 2 reduces pa into ssn and
-// pb [nb][sp] into rr and forms beta, gam and *resmax (the values of launch_colreduce
-// followed by launch_cgls_scalars)
-hipError_t launch_cgls_reduce(const double *pa, int na, const double *pb, int nb, int sp, double *sc,
-                              int mode, double *resmax, hipStream_t s);
+// start: gam0 = ssn, *resmax
+hipError_t launch_cgls_start(double *sc, int sp, double *resmax, hipStream_t s);
 struct RationalScalars {
   double f0, ew, g0, g1;   // constant of f, 2 Re sum_k w_k, constant and slope of g
 };

@@ -16,7 +16,7 @@ from workloads.bsr import BSR
 pytestmark = pytest.mark.gpu
 
 CASES = [(nb, s, ppl, rows) for nb, s in ((1, 3), (37, 5), (37, 130)) for ppl in (1, 2) for rows in (1, 2)]
-CASES += [(2, 64, -1, -1), (37, 64, -1, -1), (300, 70, -1, -1)]
+CASES += [(2, 64, -1, -1), (37, 64, -1, -1), (300, 70, -1, -1), (260, 900, -1, -1)]  # the last: vectors over 16 MiB
 
 
 @pytest.mark.parametrize("overlap", [False, True])
