@@ -415,7 +415,7 @@ int fermi_moments_batches(rfo_ctx *ctx, int64_t p, const std::vector<std::pair<i
   std::swap(ctx->moments, mom_all);
   double *obs = P<double>(ctx->small);
   HIPCHK(rfo::launch_traces(P<double>(ctx->moments), P<double>(ctx->w), P<double>(ctx->coef), p,
-                            ctx->sp, obs, ctx->stream));
+                            ctx->sp, P<double>(ctx->samples), obs, ctx->stream));
   ctx->has_q = false;
   ctx->has_dens = dens;
   if (dens) {
@@ -451,7 +451,7 @@ int rfo_fermi_moments(rfo_ctx *ctx, double T, double mu, int64_t n_terms, double
                   !dens && ctx->doubling && !ctx->has_s));
   double *obs = P<double>(ctx->small);
   HIPCHK(rfo::launch_traces(P<double>(ctx->moments), P<double>(ctx->w), P<double>(ctx->coef),
-                            n_terms, ctx->sp, obs, ctx->stream));
+                            n_terms, ctx->sp, P<double>(ctx->samples), obs, ctx->stream));
   ctx->has_q = false;
   ctx->has_dens = false;
   if (dens) {
@@ -503,7 +503,7 @@ int rfo_traces_at(rfo_ctx *ctx, double T, double mu, double *NEF_out) {
                                   P<double>(ctx->costab), P<double>(ctx->coef), ctx->stream));
   double *obs = P<double>(ctx->small);
   HIPCHK(rfo::launch_traces(P<double>(ctx->moments), P<double>(ctx->w), P<double>(ctx->coef), p,
-                            ctx->sp, obs, ctx->stream));
+                            ctx->sp, P<double>(ctx->samples), obs, ctx->stream));
   TRY(copy_out(ctx, NEF_out, obs, 3 * sizeof(double)));
   HIPCHK(hipStreamSynchronize(ctx->stream));
   return RFO_OK;

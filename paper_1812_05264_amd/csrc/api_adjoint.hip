@@ -630,7 +630,7 @@ int rfo_energy_and_dEdH(rfo_ctx *ctx, double T, double mu, int64_t n_terms, doub
         : dbl      ? energy_grad_doubling(ctx, pl, p, false, &n_events, tail)
                    : energy_grad_direct(ctx, pl, p, false, &n_events));
     HIPCHK(rfo::launch_traces(P<double>(ctx->moments), P<double>(ctx->w), P<double>(ctx->coef), p,
-                              ctx->sp, obs, ctx->stream));
+                              ctx->sp, P<double>(ctx->samples), obs, ctx->stream));
     TRY(check_flags_and_finish(ctx, n_events));
   } else {
     // the moments of every batch are gathered into the context's [p][sp] moments for
@@ -664,7 +664,7 @@ int rfo_energy_and_dEdH(rfo_ctx *ctx, double T, double mu, int64_t n_terms, doub
     pb.restore();
     std::swap(ctx->moments, mom_all);
     HIPCHK(rfo::launch_traces(P<double>(ctx->moments), P<double>(ctx->w), P<double>(ctx->coef), p,
-                              ctx->sp, obs, ctx->stream));
+                              ctx->sp, P<double>(ctx->samples), obs, ctx->stream));
   }
   HIPCHK(rfo::launch_mirror(P<int64_t>(ctx->nz_low), ctx->n_low, P<int64_t>(ctx->tpos), ctx->bd,
                             P<double>(ctx->G), ctx->stream));

@@ -140,7 +140,7 @@ int rfo_fermi_moments_noalloc(rfo_ctx *ctx, double T, double mu, int64_t n_terms
   TRY(run_forward(ctx, pl, p, ctx->vec, false, nullptr, &n_events, ctx->doubling));
   double *obs = P<double>(ctx->small);
   HIPCHK(rfo::launch_traces(P<double>(ctx->moments), P<double>(ctx->w), P<double>(ctx->coef), p,
-                            ctx->sp, obs, ctx->stream));
+                            ctx->sp, P<double>(ctx->samples), obs, ctx->stream));
   TRY(copy_out(ctx, NEF_out, obs, 3 * sizeof(double)));
   if (moments_out) {
     const int64_t total = ctx->s * p;

@@ -168,68 +168,134 @@ hipError_t launch_probe_pack(const double *rden, int64_t n, int s_real, int sp, 
 // e_j = e_min (1 - x_j)/2 + e_max (1 + x_j)/2.  Samples of
 //   f(e) = 2/(1 + exp((e - mu)/T)) = 1 - tanh((e - mu)/(2T)),  e f(e),
 //   g(e) = -2T ln(1 + exp(-(e - mu)/T)) (stable softplus form),
-// and the table cos(pi m/(2 nq)), m < 4 nq, so that cos(pi k (j + 1/2)/nq) is
-// entry (k (2j + 1)) mod 4nq: exact argument reduction for every k.
+// and the table cos(pi m/(2 nq)), m <= nq, a quarter turn: cos(pi k (j + 1/2)/nq) is the whole turn's
+// entry (k (2j + 1)) mod 4 nq, so the argument reduction is exact for every k.
+// Node nq - 1 - j has the cosine of node j times (-1)^k, so the sums run over half the nodes: the
+// samples are kept as h_j + h_{nq-1-j} (even k, first nq/2 of nq) and h_j - h_{nq-1-j} (odd k).
 __global__ __launch_bounds__(kWG) void k_coef_samples(double e_min, double e_max, double T,
                                                       double mu, int64_t nq,
                                                       double *__restrict__ samples,
                                                       double *__restrict__ costab) {
-  for (int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; m < 4 * nq;
+  const int64_t half = nq / 2;
+  for (int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; m <= nq;
        m += (int64_t)gridDim.x * blockDim.x) {
     costab[m] = cospi((double)m / (double)(2 * nq));
-    if (m < nq) {
-      const double x = cos(M_PI * ((double)m + 0.5) / (double)nq);
-      const double e = 0.5 * e_min * (1.0 - x) + 0.5 * e_max * (1.0 + x);
-      const double f = 1.0 - tanh((e - mu) / (2.0 * T));
-      const double z = -(e - mu) / T;
-      const double softplus = fmax(z, 0.0) + log1p(exp(-fabs(z)));
-      samples[m] = f;
-      samples[nq + m] = e * f;
-      samples[2 * nq + m] = -2.0 * T * softplus;
+    if (m < half) {
+      double h[2][3];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int64_t j = t ? nq - 1 - m : m;
+        const double x = cos(M_PI * ((double)j + 0.5) / (double)nq);
+        const double e = 0.5 * e_min * (1.0 - x) + 0.5 * e_max * (1.0 + x);
+        const double f = 1.0 - tanh((e - mu) / (2.0 * T));
+        const double z = -(e - mu) / T;
+        const double softplus = fmax(z, 0.0) + log1p(exp(-fabs(z)));
+        h[t][0] = f;
+        h[t][1] = e * f;
+        h[t][2] = -2.0 * T * softplus;
+      }
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        samples[i * nq + m] = h[0][i] + h[1][i];
+        samples[i * nq + half + m] = h[0][i] - h[1][i];
+      }
     }
   }
 }
 
-// c_k = (2 - delta_k0)/nq sum_j h(e_j) cos(pi k (j + 1/2)/nq), one workgroup per k
-__global__ __launch_bounds__(kWG) void k_coefs(const double *__restrict__ samples,
-                                               const double *__restrict__ costab, int64_t nq,
-                                               int64_t p, double *__restrict__ coef) {
-  const int64_t k = blockIdx.x;
-  const int64_t M = 4 * nq;
-  double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-  for (int64_t j = threadIdx.x; j < nq; j += blockDim.x) {
-    const double cv = costab[(k * (2 * j + 1)) % M];
-    s0 = fma(samples[j], cv, s0);
-    s1 = fma(samples[nq + j], cv, s1);
-    s2 = fma(samples[2 * nq + j], cv, s2);
+// c_k = (2 - delta_k0)/nq sum_j h(e_j) cos(pi k (j + 1/2)/nq), a workgroup of NTHR threads per four k of
+// one parity (the grid is even, so all its k have it).  The p * nq/2 scattered table reads are what
+// costs, so the table is in LDS where it fits (NTAB entries; 0: read from memory): k (2j + 1) has k's
+// parity, and so has every fold of it into the quarter turn, so every other entry will do.
+// 1,024 terms: 21 us with one k per workgroup and the whole table in memory, 9.7 now; 4,000 terms: 290
+// and 47.
+template <int NTAB, int NTHR>
+__global__ __launch_bounds__(NTHR) void k_coefs(const double *__restrict__ samples,
+                                                const double *__restrict__ costab, int64_t nq,
+                                                int64_t p, double *__restrict__ coef) {
+  constexpr int K = 4, W = NTHR / 64;
+  // one slot in 33 unused: the lanes of a wave are k entries apart
+  __shared__ double tab[NTAB > 0 ? NTAB + NTAB / 32 : 1];
+  auto slot = [](uint32_t i) { return i + (i >> 5); };
+  __shared__ double red[3 * K][W];
+  if (NTAB > 0) {
+    const int odd = blockIdx.x & 1;
+#pragma unroll 8
+    for (int m = threadIdx.x; 2 * m + odd <= (int)nq; m += NTHR) tab[slot(m)] = costab[2 * m + odd];
+    __syncthreads();
   }
-  s0 = wave_sum(s0);
-  s1 = wave_sum(s1);
-  s2 = wave_sum(s2);
-  __shared__ double red[3][kWaves];
+  const uint32_t M = (uint32_t)(4 * nq), half = (uint32_t)(nq / 2), quarter = (uint32_t)nq;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (lane == 0) {
-    red[0][wave] = s0;
-    red[1][wave] = s1;
-    red[2][wave] = s2;
-  }
-  __syncthreads();
-  if (threadIdx.x < 3) {
-    double t = 0.0;
-    for (int w = 0; w < kWaves; ++w) t += red[threadIdx.x][w];
-    coef[threadIdx.x * p + k] = (k == 0 ? 1.0 : 2.0) / (double)nq * t;
+  const int64_t groups = (p + 7) / 8 * 2;
+  for (int64_t g = blockIdx.x; g < groups; g += gridDim.x) {
+    const int64_t k0 = (g >> 1) * 8 + (g & 1);
+    uint32_t at[K], by[K];  // table position of the thread's node, and its advance per NTHR nodes
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+      const uint32_t k = (uint32_t)(k0 + 2 * u);  // < 2^20 + 8: the products fit 32 bits
+      at[u] = k * (2 * threadIdx.x + 1) % M;
+      by[u] = k * (2 * NTHR) % M;
+    }
+    const double *h = samples + ((g & 1) ? half : 0);
+    double s[3][K];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int u = 0; u < K; ++u) s[i][u] = 0.0;
+#pragma unroll 4
+    for (uint32_t j = threadIdx.x; j < half; j += NTHR) {
+      double hv[3];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) hv[i] = h[i * nq + j];
+#pragma unroll
+      for (int u = 0; u < K; ++u) {
+        uint32_t m = at[u];
+        const uint32_t next = m + by[u];
+        at[u] = min(next, next - M);           // next - M wraps to the top where next < M
+        m = min(m, M - m);                     // cos(-t) = cos t
+        const bool neg = m > quarter;          // cos(pi - t) = -cos t
+        m = min(m, 2 * quarter - m);
+        const double v = NTAB > 0 ? tab[slot(m >> 1)] : costab[m];
+        const double cv = neg ? -v : v;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) s[i][u] = fma(hv[i], cv, s[i][u]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int u = 0; u < K; ++u) {
+        const double v = wave_sum(s[i][u]);
+        if (lane == 0) red[i * K + u][wave] = v;
+      }
+    __syncthreads();
+    if (threadIdx.x < 3 * K) {
+      const int i = threadIdx.x / K;
+      const int64_t k = k0 + 2 * (threadIdx.x % K);
+      double t = 0.0;
+      for (int w = 0; w < W; ++w) t += red[threadIdx.x][w];
+      if (k < p) coef[i * p + k] = (k == 0 ? 1.0 : 2.0) / (double)nq * t;
+    }
+    __syncthreads();
   }
 }
 
 hipError_t launch_coefficients(double e_min, double e_max, double T, double mu, int64_t p,
                                int64_t nq, double *samples, double *costab, double *coef,
                                hipStream_t s) {
-  int64_t blocks = (4 * nq + kWG - 1) / kWG;
+  if (nq % 2 != 0 || nq < 2 || p > (1 << 20)) return hipErrorInvalidValue;
+  int64_t blocks = (nq + kWG) / kWG;
   if (blocks > 65536) blocks = 65536;
   hipLaunchKernelGGL(k_coef_samples, dim3((unsigned)blocks), dim3(kWG), 0, s, e_min, e_max, T,
                      mu, nq, samples, costab);
-  hipLaunchKernelGGL(k_coefs, dim3((unsigned)p), dim3(kWG), 0, s, samples, costab, nq, p,
-                     coef);
+  const unsigned groups = (unsigned)((p + 7) / 8 * 2);
+  if (nq <= 8192)  // 32 KB of LDS: several workgroups per compute unit
+    hipLaunchKernelGGL((k_coefs<4097, 256>), dim3(groups), dim3(256), 0, s, samples, costab, nq, p, coef);
+  else if (nq <= 32768)  // 128 KB: one, which keeps its table for all its k
+    hipLaunchKernelGGL((k_coefs<16385, 1024>), dim3(std::min(groups, 256u)), dim3(1024), 0, s, samples, costab, nq, p,
+                       coef);
+  else
+    hipLaunchKernelGGL((k_coefs<0, 1024>), dim3(groups), dim3(1024), 0, s, samples, costab, nq, p, coef);
   return hipGetLastError();
 }
 
@@ -289,24 +355,31 @@ hipError_t launch_moment_reduce(const double *part, int ring, int64_t k0, int co
 }
 
 // ---- traces ----------------------------------------------------------------------
-// out = [N, E, F] = sum_k c_k sum_c w_c mu[k][c] for the three coefficient sets
+// out = [N, E, F] = sum_k c_k sum_c w_c mu[k][c] for the three coefficient sets: each wave takes every
+// (kWaves G)-th k with its lanes along the probes, the G workgroups' sums part [3][G] are added in
+// order by one more.  (One workgroup with a k per thread: 33 us for 1,024 moments of 64 probes,
+// 3.3 + 1.6 now; 4,000 of 128 probes 260 and 6.6 + 5.6.)
 __global__ __launch_bounds__(kWG) void k_traces(const double *__restrict__ moments,
                                                 const double *__restrict__ w,
                                                 const double *__restrict__ coef, int64_t p, int sp,
-                                                double *out3) {
+                                                double *__restrict__ part) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t step = (int64_t)gridDim.x * kWaves;
   double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-  for (int64_t k = threadIdx.x; k < p; k += blockDim.x) {
-    double m = 0.0;
-    for (int c = 0; c < sp; ++c) m = fma(w[c], moments[k * sp + c], m);
-    s0 = fma(coef[k], m, s0);
-    s1 = fma(coef[p + k], m, s1);
-    s2 = fma(coef[2 * p + k], m, s2);
+  for (int c = lane; c < sp; c += 64) {
+    const double wc = w[c];
+#pragma unroll 4
+    for (int64_t k = (int64_t)blockIdx.x * kWaves + wave; k < p; k += step) {
+      const double m = wc * moments[k * sp + c];
+      s0 = fma(coef[k], m, s0);
+      s1 = fma(coef[p + k], m, s1);
+      s2 = fma(coef[2 * p + k], m, s2);
+    }
   }
   s0 = wave_sum(s0);
   s1 = wave_sum(s1);
   s2 = wave_sum(s2);
   __shared__ double red[3][kWaves];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   if (lane == 0) {
     red[0][wave] = s0;
     red[1][wave] = s1;
@@ -316,13 +389,26 @@ __global__ __launch_bounds__(kWG) void k_traces(const double *__restrict__ momen
   if (threadIdx.x < 3) {
     double t = 0.0;
     for (int q = 0; q < kWaves; ++q) t += red[threadIdx.x][q];
-    out3[threadIdx.x] = t;
+    part[threadIdx.x * gridDim.x + blockIdx.x] = t;
   }
 }
 
+// one wave per sum
+__global__ __launch_bounds__(192) void k_traces_sum(const double *__restrict__ part, int G,
+                                                    double *__restrict__ out3) {
+  const int t = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  double v = 0.0;
+#pragma unroll 4
+  for (int g = lane; g < G; g += 64) v += part[t * G + g];
+  v = wave_sum(v);
+  if (lane == 0) out3[t] = v;
+}
+
 hipError_t launch_traces(const double *moments, const double *w, const double *coef, int64_t p,
-                         int sp, double *out3, hipStream_t s) {
-  hipLaunchKernelGGL(k_traces, dim3(1), dim3(kWG), 0, s, moments, w, coef, p, sp, out3);
+                         int sp, double *part, double *out3, hipStream_t s) {
+  const int G = traces_parts(p);
+  hipLaunchKernelGGL(k_traces, dim3(G), dim3(kWG), 0, s, moments, w, coef, p, sp, part);
+  hipLaunchKernelGGL(k_traces_sum, dim3(1), dim3(192), 0, s, part, G, out3);
   return hipGetLastError();
 }
 

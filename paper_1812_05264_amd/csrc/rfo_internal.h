@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace rfo {
 
 constexpr int kWG = 256;            // threads per workgroup (4 wave64)
@@ -130,7 +132,7 @@ hipError_t launch_gershgorin(const double *h, const int64_t *row_ptr,
 // Probe classification (all +-1?) and packing to sign bits.
 hipError_t launch_probe_pack(const double *rden, int64_t n, int s_real, int sp,
                              uint64_t *sgn, int *flags, hipStream_t st);
-// Chebyshev coefficients of f, x f, g by Chebyshev-Gauss quadrature.
+// Chebyshev coefficients of f, x f, g by Chebyshev-Gauss quadrature over nq nodes (even).
 hipError_t launch_coefficients(double e_min, double e_max, double T, double mu,
                                int64_t p, int64_t nq, double *samples,
                                double *costab, double *coef, hipStream_t s);
@@ -143,9 +145,11 @@ hipError_t launch_moment_reduce(const double *part, int ring, int64_t k0,
                                 int count, int n_rg, int sp, double *moments,
                                 int check, double tol, int *flags, int dbl,
                                 hipStream_t s);
-// N, E, F from moments and coefficients.
+// N, E, F from moments and coefficients; part: 3 * traces_parts(p) doubles of work memory (the
+// coefficient samples, 3 nq doubles, are free by then).
+inline int traces_parts(int64_t p) { return (int)std::min<int64_t>(256, (p + 3) / 4); }
 hipError_t launch_traces(const double *moments, const double *w,
-                         const double *coef, int64_t p, int sp, double *out3,
+                         const double *coef, int64_t p, int sp, double *part, double *out3,
                          hipStream_t s);
 // Masked outer products on the block pattern:
 //   G[nz] (+)= sum_t coef_t sum_c w_c X_t[I-block][c] Y_t[J-block][c]
