@@ -174,6 +174,46 @@ int rfo_set_hamiltonian(rfo_ctx *ctx, int64_t n_block_rows, int block_dim, const
     ctx->n_grp_up = (int64_t)gu.size() - 1;
     ctx->n_grp_all = (int64_t)ga.size() - 1;
 
+    // small matrices of 1x1 blocks: rows sorted by length (stable) in slices of 64, a slice as wide as
+    // its longest row in pairs of entries
+    ctx->run_ns = 0;
+    std::vector<int32_t> slice, perm, src;
+    std::vector<uint32_t> cols;
+    if (block_dim == 1 && nb <= rfo::run_rows(4)) {
+      const int ns = (int)((nb + 63) / 64);
+      std::vector<int64_t> start(ctx->max_row + 2, 0);
+      auto len = [&](int64_t I) { return row_ptr[I + 1] - row_ptr[I]; };
+      for (int64_t I = 0; I < nb; ++I) ++start[ctx->max_row - len(I) + 1];
+      for (int64_t k = 1; k < (int64_t)start.size(); ++k) start[k] += start[k - 1];
+      perm.assign((size_t)ns * 64, -1);
+      for (int64_t I = 0; I < nb; ++I) perm[start[ctx->max_row - len(I)]++] = (int32_t)I;
+      slice.assign(1, 0);
+      for (int t = 0; t < ns; ++t) slice.push_back(slice.back() + (int32_t)((len(perm[t * 64]) + 1) / 2));
+      src.assign((size_t)slice.back() * 128, -1);
+      cols.assign((size_t)slice.back() * 64, 0);
+      for (int t = 0; t < ns; ++t)
+        for (int l = 0; l < 64; ++l) {
+          const int32_t I = perm[t * 64 + l];
+          if (I < 0) continue;
+          for (int64_t z = row_ptr[I]; z < row_ptr[I + 1]; ++z) {
+            const int64_t k = z - row_ptr[I], e = ((int64_t)slice[t] + k / 2) * 64 + l;
+            src[2 * e + k % 2] = (int32_t)z;
+            cols[e] |= (uint32_t)col_idx[z] << (16 * (k % 2));
+          }
+        }
+      auto upload = [&](DevBuf &b, const void *p, size_t bytes) -> int {
+        TRY(ensure(ctx, b, bytes));
+        HIPCHK(hipMemcpyAsync(b.p, p, bytes, hipMemcpyHostToDevice, ctx->stream));
+        return RFO_OK;
+      };
+      TRY(upload(ctx->run_slice, slice.data(), slice.size() * sizeof(int32_t)));
+      TRY(upload(ctx->run_perm, perm.data(), perm.size() * sizeof(int32_t)));
+      TRY(upload(ctx->run_cols, cols.data(), cols.size() * sizeof(uint32_t)));
+      TRY(upload(ctx->run_src, src.data(), src.size() * sizeof(int32_t)));
+      ctx->run_ns = ns;
+      ctx->run_pairs = slice.back();
+      ctx->run_max = (int)((ctx->max_row + 1) / 2);
+    }
     HIPCHK(hipStreamSynchronize(ctx->stream));  // host vectors go out of scope
   }
   ctx->has_h = false;
@@ -259,6 +299,17 @@ int rfo_set_hamiltonian(rfo_ctx *ctx, int64_t n_block_rows, int block_dim, const
                          P<int64_t>(ctx->tpos), ctx->nnzb, ctx->bd, e_min, e_max,
                          P<double>(ctx->h64), precision == RFO_FP32 ? P<float>(ctx->h32) : nullptr,
                          P<int>(ctx->flags), ctx->stream));
+  ctx->run_slices = 0;
+  if (ctx->run_ns > 0 && !is_bf16(precision)) {
+    const int vt = precision == RFO_FP64 ? 8 : 4;
+    if (ctx->nb <= rfo::run_rows(vt)) {
+      TRY(ensure(ctx, ctx->run_vals, (size_t)ctx->run_pairs * 128 * vt));
+      HIPCHK(rfo::launch_run_fill(kernel_precision(ctx), precision == RFO_FP64 ? ctx->h64.p : ctx->h32.p,
+                                  P<int32_t>(ctx->run_src), (int64_t)ctx->run_pairs * 128, ctx->run_vals.p,
+                                  ctx->stream));
+      ctx->run_slices = ctx->run_ns;
+    }
+  }
   if (is_bf16(precision))
     HIPCHK(rfo::launch_pack_bf16(P<double>(ctx->h64), P<int32_t>(ctx->kc_src), ctx->n_chunks,
                                  precision == RFO_BF16X2 ? 1 : 0, ctx->hbf16.p, ctx->stream));
@@ -440,7 +491,7 @@ int rfo_fermi_moments(rfo_ctx *ctx, double T, double mu, int64_t n_terms, double
   // a last probe tile of 128 columns with at most 64 real probes runs as a batch
   // of its own, 64 columns wide
   const auto batches = last_tile_batches(ctx);
-  if (!batches.empty()) return fermi_moments_batches(ctx, n_terms, batches, moments_out, NEF_out, density_out);
+  if (!batches.empty() && !run_resident(ctx, density_out != nullptr)) return fermi_moments_batches(ctx, n_terms, batches, moments_out, NEF_out, density_out);
   const bool dens = density_out != nullptr;
   // vector slots: y pair; with an overlap also t and the CG vectors r, p, q
   TRY(ensure(ctx, ctx->vec, (ctx->has_s ? 6 : 2) * pl.slot_bytes));

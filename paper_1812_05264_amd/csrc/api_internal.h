@@ -44,6 +44,11 @@ struct rfo_ctx {
   // 9x9 FP64/FP32 outer products: groups of the upper blocks and of all blocks
   DevBuf grp_up, grp_all;
   int64_t n_grp_up = 0, n_grp_all = 0;
+  // small matrices of 1x1 blocks: rows sorted by length in slices of 64 (RunArgs), the nonzero of each
+  // slot and the values in the precision of the steps
+  DevBuf run_slice, run_perm, run_cols, run_src, run_vals;
+  int run_ns = 0, run_slices = 0;  // slices of the pattern; 0 where the steps run one by one
+  int run_pairs = 0, run_max = 0;  // entry pairs, and of the widest slice
   // BF16 steps: K chunks of 16 rows per block row (first chunk of each row,
   // gathered row J*9 + c and source nz*9 + c of every K row)
   DevBuf kc_ptr, kc_idx, kc_src;
@@ -99,6 +104,7 @@ struct rfo_ctx {
     hipSetDevice(device);
     DevBuf *all[] = {&row_ptr, &col, &brow, &tpos, &hraw, &h64, &h32, &hbf16, &gscratch, &nz_up, &nz_low,
                      &kc_ptr, &kc_idx, &kc_src, &up_grp, &grp_up, &grp_all,
+                     &run_slice, &run_perm, &run_cols, &run_src, &run_vals,
                      &s64, &cg_part, &cg_sc, &cg_spart, &GQ, &rat, &rat_part, &rat_sc, &rat_rho, &rat_coef,
                      &sgn, &rden, &w, &vec, &acc, &ring, &moments, &coef, &samples,
                      &costab, &small, &flags, &G, &dHdR, &forces};
@@ -525,6 +531,18 @@ inline int cg_solve(rfo_ctx *ctx, const Plan &pl, DevBuf &bufs, const void *y, v
               max_it);
 }
 
+// The whole forward pass in one launch.  FP32 with dense probes and a density goes step by step: the
+// probes in FP64 and the accumulator do not both fit the two vector slots that serve as work memory.
+inline bool run_resident(const rfo_ctx *ctx, bool use_acc) {
+  if (ctx->bd != 1 || ctx->has_s || ctx->run_slices == 0) return false;
+  if (ctx->prec == RFO_FP32 && !ctx->signs && use_acc) return false;
+  // many rows on few compute units: a launch per step spreads them better (FP32, us one launch / one per step:
+  // 10,648 rows and 64 probes 876 / 988, 12,167 and 10 2,135 / 1,929, 13,824 and 64 1,119 / 1,070, 17,576 and
+  // 128 1,372 / 1,400)
+  if (ctx->n > 11264 && ctx->s < 128) return false;
+  return true;
+}
+
 inline int run_forward(rfo_ctx *ctx, const Plan &pl, int64_t p, DevBuf &bufs, bool use_acc,
                 const Checkpoints *ck, size_t *n_events, bool dbl = false) {
   if (dbl && use_acc) return fail(ctx, RFO_E_INVALID, "the density needs every y_k");
@@ -558,6 +576,44 @@ inline int run_forward(rfo_ctx *ctx, const Plan &pl, int64_t p, DevBuf &bufs, bo
     }
     return RFO_OK;
   };
+
+  if (!ck && run_resident(ctx, use_acc)) {
+    rfo::RunArgs ra;
+    memset(&ra, 0, sizeof(ra));
+    ra.slice = P<int32_t>(ctx->run_slice);
+    ra.perm = P<int32_t>(ctx->run_perm);
+    ra.cols = P<uint32_t>(ctx->run_cols);
+    ra.vals = ctx->run_vals.p;
+    ra.n = (int)ctx->n;
+    ra.n_slices = ctx->run_slices;
+    ra.sgn = ctx->signs ? P<uint64_t>(ctx->sgn) : nullptr;
+    ra.rden = ctx->signs ? nullptr : P<double>(ctx->rden);
+    ra.s = (int)ctx->s;
+    ra.sp = ctx->sp;
+    ra.steps = dbl ? p / 2 : p - 1;
+    ra.p = p;
+    ra.moments = mom;
+    ra.coef = coef;
+    ra.acc = accp;
+    ra.work = accp ? A : nullptr;
+    if (!ctx->signs && !dbl) ra.rwork = reinterpret_cast<double *>(use_acc ? B : A);
+    ra.tol = tol;
+    ra.flags = flags;
+    size_t ev = 0;
+    auto mark = [&]() -> int {
+      if (!ctx->timing) return RFO_OK;
+      hipEvent_t e = next_event(ctx, ev++);
+      if (!e) return fail(ctx, RFO_E_DEVICE, "hipEventCreate failed");
+      HIPCHK(hipEventRecord(e, ctx->stream));
+      return RFO_OK;
+    };
+    TRY(mark());
+    HIPCHK(rfo::launch_run(kp, use_acc ? 1 : dbl ? 2 : 0, ctx->run_max, ra, ctx->stream));
+    TRY(mark());
+    if (ctx->timing) ctx->t_steps += ra.steps;
+    *n_events = ev;
+    return RFO_OK;
+  }
 
   rfo::InitArgs ia;
   fill_init(ctx, pl, ia);

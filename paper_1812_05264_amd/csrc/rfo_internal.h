@@ -81,6 +81,33 @@ inline int step_mode(const StepArgs &a) {
 hipError_t launch_step(int precision, int ppl, const StepArgs &a, hipStream_t s);
 hipError_t launch_step9(int precision, int nt, const StepArgs &a, hipStream_t s);
 
+// All steps of a small matrix of 1x1 blocks in one launch (k_run1.hip).
+constexpr int kRunWaves = 16;
+// most rows: two vectors in LDS beside 10 KB of moment sums, 16-bit columns, 32 rows a thread
+inline int64_t run_rows(int vt_bytes) { return std::min<int64_t>((160 - 10) * 1024 / (2 * vt_bytes), 32 * 64 * kRunWaves); }
+struct RunArgs {
+  const int32_t *slice;    // first entry pair of each slice of 64 rows [n_slices + 1]
+  const int32_t *perm;     // row of each slot [64 n_slices], -1 past the last
+  const uint32_t *cols;    // [pairs][64] two columns
+  const void *vals;        // [pairs][64] two entries of H_hat
+  int n, n_slices;
+  const uint64_t *sgn;     // probes, as in the step kernels
+  const double *rden;
+  int s, sp;               // real and padded columns
+  int64_t steps, p;
+  double *moments;         // [p][sp]
+  const double *coef;      // mode 1: alpha^f
+  void *acc;               // mode 1: P r [n][sp]
+  void *work;              // mode 1: [s][n] in the vectors' type
+  double *rwork;           // modes 0 and 1, dense probes: [s][n]
+  double tol;              // flags bit 2: a moment above (1 + tol) moment 0
+  int *flags;
+};
+// mode 0: moments r . y_k; 1: those and the density accumulator; 2: moments by doubling
+hipError_t launch_run(int precision, int mode, int max_pairs, const RunArgs &a, hipStream_t s);
+// dst[e] = h[src[e]] or zero
+hipError_t launch_run_fill(int precision, const void *h, const int32_t *src, int64_t n, void *dst, hipStream_t s);
+
 // y = scale * r (+ acc = alpha * r, + part = r . y) with the step kernel's decomposition
 struct InitArgs {
   void *out;
