@@ -27,23 +27,35 @@ __device__ __forceinline__ int xcd_logical(int b, int nwg) {
 // step that follows one sweeping forward then first reads the rows its
 // predecessor touched last, while the memory-side cache still holds them.
 struct Sched {
-  int64_t i, hi, lo, n_rg;
-  int stride;
+  int64_t i, hi;
+  int rg_, n_rg, stride, pt_;
   bool rev;
-  __device__ Sched(int n_pt, int64_t n_rg_, bool rev_ = false) : n_rg(n_rg_), rev(rev_) {
+  __device__ Sched(int n_pt, int n_rg_in, bool rev_ = false) : n_rg(n_rg_in), rev(rev_) {
     const int b = blockIdx.x, G = gridDim.x;
     const int x = b & 7;
     const int64_t U = (int64_t)n_pt * n_rg;
     stride = G >> 3;
-    lo = U * x / 8;
+    const int64_t lo = U * x / 8;
     i = lo + (b >> 3);
     hi = U * (x + 1) / 8;
+    const int64_t unit = i >= hi ? 0 : rev ? lo + hi - 1 - i : i;
+    pt_ = (int)(unit / n_rg);
+    rg_ = (int)(unit - (int64_t)pt_ * n_rg);
   }
   __device__ bool more() const { return i < hi; }
-  __device__ void next() { i += stride; }
-  __device__ int64_t unit() const { return rev ? lo + hi - 1 - i : i; }
-  __device__ int pt() const { return (int)(unit() / n_rg); }
-  __device__ int64_t rg() const { return unit() - (int64_t)pt() * n_rg; }
+  // tile and row group move along with the unit: a division for each took as many instructions as a
+  // row of a 7-point stencil (steps of 1x1 blocks, us: 110,592 rows and 64 probes, FP64 52.3 -> 50.2, 32,768
+  // and 100, FP32 19.3 -> 18.7; 262,144 and 256, FP64 404 -> 402)
+  __device__ void next() {
+    i += stride;
+    if (rev) {
+      for (rg_ -= stride; rg_ < 0; rg_ += n_rg) --pt_;
+    } else {
+      for (rg_ += stride; rg_ >= n_rg; rg_ -= n_rg) ++pt_;
+    }
+  }
+  __device__ int pt() const { return pt_; }
+  __device__ int64_t rg() const { return rg_; }
 };
 
 template <typename T, int N>
