@@ -165,6 +165,21 @@ __device__ __forceinline__ VecN<VT, N> add_terms(VecN<VT, N> av, int m, const VT
   return av;
 }
 
+// the value of lane ^ W in a quad
+template <int W>
+__device__ __forceinline__ unsigned quad_xor(unsigned v) {
+  constexpr int perm = W == 1 ? 0xb1 : 0x4e;  // quad_perm [1, 0, 3, 2], [2, 3, 0, 1]
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, perm, 0xf, 0xf, true);
+}
+// One exchange of a transpose within quads (up: the lane's bit W): x of the lanes with the bit and y of
+// those without change places
+template <int W>
+__device__ __forceinline__ void quad_swap(unsigned &x, unsigned &y, bool up) {
+  const unsigned fx = quad_xor<W>(y), fy = quad_xor<W>(x);
+  x = up ? fx : x;
+  y = up ? y : fy;
+}
+
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // BF16 bits of an FP32 value, rounded to nearest even.

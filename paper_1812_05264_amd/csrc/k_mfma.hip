@@ -24,6 +24,8 @@
 // kc_idx lists the 32 gathered rows J*9 + c and the A operands are pre-packed:
 // entry g*9 + m (m < 9) holds the eight BF16 values H_hat_IJ[m][c] of K rows
 // 8g .. 8g+7; lanes with m > 8 supply zeros.
+#include <type_traits>
+
 #include "device_util.h"
 #include "rfo_internal.h"
 
@@ -283,13 +285,138 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
 // row, so X_I and Y_I are loaded once for all of them; each block keeps a 16 x 16
 // FP32 tile (4 registers per lane), flushed into FP64 sums after every step t.
 // Lane l supplies A[l%16][8(l/16)..+7] and B[8(l/16)..+7][l%16] and holds
-// D[4(l/16)+i][l%16] (layout checked on the device); a lane loads 8 consecutive
-// probes of a row with one 16-byte access, which are its eight K slots as they
-// stand, the same probes in A and B.  Four waves per SIMD requested from the
-// compiler (no spills; the default took three waves).
+// D[4(l/16)+i][l%16] (layout checked on the device); which probe a K slot is does not matter
+// as long as A and B agree.  Loaded as the instruction wants them, four neighbouring lanes would read
+// four rows (144 cache accesses per operand and 128 probes); a quad of lanes instead reads 64
+// contiguous bytes of each of its four rows in turn (36) and transposes them in its registers: after it
+// lane r has row r's 16 bytes of four K sets.  What is left is bound by the rows' bytes from beyond
+// the L2 and by these exchanges: 16,000 atoms, 256 probes, 1,000 terms 489 -> 447 ms per gradient;
+// 4,000 atoms, 128 probes, 130 terms 9.9 -> 9.3.  Three waves per SIMD (161 registers).
 // ---------------------------------------------------------------------------
+namespace {
+
+struct Rows4 {
+  uint4 v[4];  // K sets 0..3 of the lane's row
+};
+
+// rows 4 a + j (a = quad % 4) of the block row at B, probes c0 + 8 (4 (quad / 4) + lane % 4)..+7
+__device__ __forceinline__ Rows4 rows4(const unsigned short *B, int sp, int c0, int lane) {
+  const int quad = lane >> 2, a4 = (quad & 3) * 4;
+  const int c = c0 + 32 * (quad >> 2) + 8 * (lane & 3);
+  Rows4 r;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    r.v[j] = make_uint4(0, 0, 0, 0);
+    if (a4 + j < 9 && c < sp) r.v[j] = *reinterpret_cast<const uint4 *>(B + (a4 + j) * sp + c);
+  }
+  return r;
+}
+
+__device__ __forceinline__ void transpose4(Rows4 &r, int lane) {
+  const bool odd = lane & 1, high = lane & 2;
+  auto pair = [&](uint4 &x, uint4 &y, auto wc, bool up) {
+    constexpr int W = decltype(wc)::value;
+    quad_swap<W>(x.x, y.x, up);
+    quad_swap<W>(x.y, y.y, up);
+    quad_swap<W>(x.z, y.z, up);
+    quad_swap<W>(x.w, y.w, up);
+  };
+  pair(r.v[0], r.v[1], std::integral_constant<int, 1>{}, odd);
+  pair(r.v[2], r.v[3], std::integral_constant<int, 1>{}, odd);
+  pair(r.v[0], r.v[2], std::integral_constant<int, 2>{}, high);
+  pair(r.v[1], r.v[3], std::integral_constant<int, 2>{}, high);
+}
+
+}  // namespace
+
 template <int GB>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k_sddmm_bf16(SddmmMfmaArgs a) {
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k_sddmm_bf16(SddmmMfmaArgs a) {
+  const int wave = uniform(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int64_t gi = (int64_t)xcd_logical(blockIdx.x, gridDim.x) * kWaves + wave;
+  if (gi >= a.n_grp) return;
+  const int64_t q0 = sld(a.grp + gi), q1 = sld(a.grp + gi + 1);
+  const int nb = (int)(q1 - q0);
+  const int m = lane & 15, kq = lane >> 4;
+  int64_t nzs[GB], js[GB];
+#pragma unroll
+  for (int g = 0; g < GB; ++g) {
+    nzs[g] = sld(a.nzlist + (g < nb ? q0 + g : q0));
+    js[g] = sld(a.col + nzs[g]);
+  }
+  const int64_t I = sld(a.brow + nzs[0]);
+  const int sp = a.sp;
+  double acc[GB][4];
+#pragma unroll
+  for (int g = 0; g < GB; ++g)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[g][r] = 0.0;
+
+  for (int t = 0; t < a.count; ++t) {
+    const unsigned short *X = static_cast<const unsigned short *>(a.xbase) + (int64_t)t * a.xstride;
+    const unsigned short *Y = static_cast<const unsigned short *>(a.ybase) + (int64_t)t * a.ystride;
+    f4 d[GB];
+#pragma unroll
+    for (int g = 0; g < GB; ++g) d[g] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int c0 = 0; c0 < sp; c0 += 128) {
+      // A operands X_I, Y_I (zero rows 9..15 and zero probes past s_real)
+      Rows4 xa = rows4(X + I * 9 * sp, sp, c0, lane), ya = rows4(Y + I * 9 * sp, sp, c0, lane);
+      if (c0 + 128 > a.s_real) {
+        auto mask = [&](unsigned &v, int c) {
+          if (c >= a.s_real) v = 0;
+          else if (c + 1 >= a.s_real) v &= 0xffffu;
+        };
+        const int c = c0 + 32 * kq + 8 * (lane & 3);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          mask(xa.v[j].x, c), mask(xa.v[j].y, c + 2), mask(xa.v[j].z, c + 4), mask(xa.v[j].w, c + 6);
+          mask(ya.v[j].x, c), mask(ya.v[j].y, c + 2), mask(ya.v[j].z, c + 4), mask(ya.v[j].w, c + 6);
+        }
+      }
+      transpose4(xa, lane);
+      transpose4(ya, lane);
+#pragma unroll
+      for (int g = 0; g < GB; ++g) {
+        if (g < nb) {
+          Rows4 yj = rows4(Y + js[g] * 9 * sp, sp, c0, lane), xj = rows4(X + js[g] * 9 * sp, sp, c0, lane);
+          transpose4(yj, lane);
+          transpose4(xj, lane);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            d[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, xa.v[i]),
+                                                           __builtin_bit_cast(bf8, yj.v[i]), d[g], 0, 0, 0);
+            d[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, ya.v[i]),
+                                                           __builtin_bit_cast(bf8, xj.v[i]), d[g], 0, 0, 0);
+          }
+        }
+      }
+    }
+    const double coef = a.scale * a.w0 * ((a.j0 + t == 0) ? a.first : a.rest);
+#pragma unroll
+    for (int g = 0; g < GB; ++g)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[g][r] = fma(coef, (double)d[g][r], acc[g][r]);
+  }
+  // lane holds G_IJ[4 kq + r][m] of every block of the group
+#pragma unroll
+  for (int g = 0; g < GB; ++g) {
+    if (g < nb) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 4 * kq + r;
+        if (row < 9 && m < 9) {
+          double *gp = a.G + nzs[g] * 81 + row * 9 + m;
+          *gp = a.accumulate ? *gp + acc[g][r] : acc[g][r];
+        }
+      }
+    }
+  }
+}
+
+// The same for 64 padded probes, loaded as the instruction wants them: half of the K sets above would be
+// empty (1,000 atoms, 64 probes, 130 terms: 3.32 ms per gradient there, 3.12 here).
+template <int GB>
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k_sddmm_bf16_64(SddmmMfmaArgs a) {
   constexpr int P = 8;  // probes per lane per load (16 bytes of BF16)
   const int wave = uniform(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
@@ -382,7 +509,8 @@ hipError_t launch_sddmm_bf16(const SddmmMfmaArgs &a, hipStream_t s) {
   if (a.n_grp == 0) return hipSuccess;
   if (a.sp % 32 != 0) return hipErrorInvalidValue;  // 32 probes per load round of a wave
   const dim3 grid((unsigned)((a.n_grp + kWaves - 1) / kWaves));
-  hipLaunchKernelGGL((k_sddmm_bf16<kSddmmGroup>), grid, dim3(kWG), 0, s, a);
+  if (a.sp % 128 == 0) hipLaunchKernelGGL((k_sddmm_bf16<kSddmmGroup>), grid, dim3(kWG), 0, s, a);
+  else hipLaunchKernelGGL((k_sddmm_bf16_64<kSddmmGroup>), grid, dim3(kWG), 0, s, a);
   return hipGetLastError();
 }
 

@@ -39,12 +39,6 @@ constexpr int kMaxWaves9 = 8;
 
 typedef const __attribute__((address_space(1))) char *GlobalBytes;
 
-// the value of lane ^ W in a quad
-template <int W>
-__device__ __forceinline__ unsigned quad_xor(unsigned v) {
-  constexpr int perm = W == 1 ? 0xb1 : 0x4e;  // quad_perm [1, 0, 3, 2], [2, 3, 0, 1]
-  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, perm, 0xf, 0xf, true);
-}
 template <int I>
 __device__ __forceinline__ unsigned quad_lane(unsigned v) {  // the value of lane I of the quad
   return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, I * 0x55, 0xf, 0xf, true);
@@ -70,20 +64,14 @@ struct Raw9 {
 template <typename VT>
 __device__ __forceinline__ void quad_transpose(Raw9<VT> &a, int lane) {
   const bool odd = lane & 1, high = lane & 2;
-  auto swap = [](unsigned &x, unsigned &y, bool up, auto wc) {
-    constexpr int W = decltype(wc)::value;
-    const unsigned fx = quad_xor<W>(y), fy = quad_xor<W>(x);
-    x = up ? fx : x;
-    y = up ? y : fy;
-  };
 #pragma unroll
   for (int w = 0; w < (int)sizeof(VT) / 4; ++w)
 #pragma unroll
     for (int b = 0; b < 8; b += 4) {
 #pragma unroll
-      for (int j = 0; j < 4; j += 2) swap(a.v[b + j][w], a.v[b + j + 1][w], odd, std::integral_constant<int, 1>{});
+      for (int j = 0; j < 4; j += 2) quad_swap<1>(a.v[b + j][w], a.v[b + j + 1][w], odd);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) swap(a.v[b + j][w], a.v[b + j + 2][w], high, std::integral_constant<int, 2>{});
+      for (int j = 0; j < 2; ++j) quad_swap<2>(a.v[b + j][w], a.v[b + j + 2][w], high);
     }
 }
 
