@@ -367,12 +367,12 @@ int rfo_set_moment_doubling(rfo_ctx *ctx, int enabled);
  *   RFO_TUNE_ROWS_PER_WG    block rows per scheduling unit of the step kernels (>= 1)
  *   RFO_TUNE_GRID           resident workgroups of the step kernels (>= 8, rounded to 8)
  *   RFO_TUNE_BF16_CHUNKS    BF16 steps: K chunks of 32 rows per iteration (1, 2)
- *   RFO_TUNE_SDDMM_PPL      probes per lane of the vector-unit outer products (1, 2)
- *   RFO_TUNE_SDDMM_MFMA     0 keeps the BF16 segment gradient on the vector units (it then
- *                           reads the FP32 vectors instead of their BF16 copies)
- *   RFO_TUNE_SDDMM_STEPS    steps per launch of the segment gradient on the vector units
+ *   RFO_TUNE_SDDMM_PPL      probes per lane of the outer products of 1x1 blocks (1, 2)
+ *   RFO_TUNE_SDDMM_MFMA     0 takes the BF16 segment gradient from the FP32 vectors instead
+ *                           of their BF16 copies, with FP64 sums
+ *   RFO_TUNE_SDDMM_STEPS    steps per launch of the segment gradient of FP64 and FP32 vectors
  *                           (default 32; 0 = one launch per segment)
- *   RFO_TUNE_SDDMM_STEPS_BF16  the same for the matrix-core segment gradient (default 8)
+ *   RFO_TUNE_SDDMM_STEPS_BF16  the same for the BF16 segment gradient (default 8)
  *   RFO_TUNE_OVERLAP        1: each segment's gradient of the doubled adjoint runs on a
  *                           second stream beside the next segment's steps (default 0; the
  *                           result is bitwise the serial one)

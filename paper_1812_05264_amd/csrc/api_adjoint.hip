@@ -610,7 +610,7 @@ int rfo_energy_and_dEdH(rfo_ctx *ctx, double T, double mu, int64_t n_terms, doub
                 "is %zu (probe batches are not taken with an overlap)", (size_t)ctx->sp * per_probe, budget);
   double *obs = P<double>(ctx->small);
   // Probe batches [c0, c0 + s_b): of `width` columns when the budget asks for them.
-  // Without that, a last VALU probe tile of 128 columns holding at most 64 real ones
+  // Without that, a last probe tile of 128 columns holding at most 64 real ones
   // runs as a batch of its own, 64 columns wide: a tile costs about the same whatever
   // part of it is live (the Hamiltonian is read and staged once per tile).
   std::vector<std::pair<int64_t, int64_t>> batches;

@@ -335,8 +335,8 @@ inline void fill_init(rfo_ctx *c, const Plan &pl, rfo::InitArgs &a) {
 
 // The segment gradient of the BF16 steps runs on the matrix cores when every real
 // probe has the same weight (the weight is applied in FP64 after each step's
-// contraction).  FP32 steps keep the VALU contraction: an FP32-MFMA version
-// measured no faster at full size and sums in FP32.
+// contraction).  FP32 steps keep FP64 sums (k_sddmm9): an FP32-MFMA version measured no faster
+// at full size and sums in FP32.
 inline bool use_mfma_sddmm(const rfo_ctx *c) {
   if (c->bd != 9 || !is_bf16(c->prec) || c->w_uniform == 0.0 || !c->has_up_grp) return false;
   if (c->sp % 32 != 0) return false;
