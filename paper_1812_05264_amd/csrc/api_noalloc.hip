@@ -49,16 +49,6 @@ __global__ void k_clear_flag(int *flag) {
   if (threadIdx.x == 0) *flag = 0;
 }
 
-// moments [p][sp] (internal) -> out [s][p] (the ABI's layout)
-__global__ __launch_bounds__(256) void k_moments_to_probe_major(const double *__restrict__ mom,
-                                                                int64_t p, int sp, int64_t s,
-                                                                double *__restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= s * p) return;
-  const int64_t c = i / p, k = i - c * p;
-  out[i] = mom[k * sp + c];
-}
-
 size_t round256(size_t b) { return (b + 255) / 256 * 256; }
 
 // The context's work buffers pointed at regions of the scratch array for the
@@ -144,9 +134,7 @@ int rfo_fermi_moments_noalloc(rfo_ctx *ctx, double T, double mu, int64_t n_terms
   TRY(copy_out(ctx, NEF_out, obs, 3 * sizeof(double)));
   if (moments_out) {
     const int64_t total = ctx->s * p;
-    k_moments_to_probe_major<<<(unsigned)((total + 255) / 256), 256, 0, ctx->stream>>>(
-        P<double>(ctx->moments), p, ctx->sp, ctx->s, mom_out_dev);
-    HIPCHK(hipGetLastError());
+    HIPCHK(rfo::launch_moments_out(P<double>(ctx->moments), p, ctx->sp, ctx->s, mom_out_dev, ctx->stream));
     TRY(copy_out(ctx, moments_out, mom_out_dev, (size_t)total * sizeof(double)));
   }
   TRY(check_flags_and_finish(ctx, 0));

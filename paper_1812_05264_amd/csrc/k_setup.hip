@@ -412,4 +412,24 @@ hipError_t launch_traces(const double *moments, const double *w, const double *c
   return hipGetLastError();
 }
 
+// moments [p][sp] -> out [s][p] in tiles of 32 x 32 through LDS
+__global__ __launch_bounds__(256) void k_moments_out(const double *__restrict__ mom, int64_t p, int sp, int64_t s,
+                                                     double *__restrict__ out) {
+  __shared__ double tile[32][33];
+  const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
+  const int64_t tiles = (s + 31) / 32, c0 = (int64_t)(blockIdx.x % tiles) * 32, k0 = (int64_t)(blockIdx.x / tiles) * 32;
+  for (int r = y; r < 32; r += 8)
+    if (k0 + r < p && c0 + x < s) tile[r][x] = mom[(k0 + r) * sp + c0 + x];
+  __syncthreads();
+  for (int r = y; r < 32; r += 8)
+    if (c0 + r < s && k0 + x < p) out[(c0 + r) * p + k0 + x] = tile[x][r];
+}
+
+hipError_t launch_moments_out(const double *moments, int64_t p, int sp, int64_t s, double *out, hipStream_t st) {
+  const int64_t blocks = (s + 31) / 32 * ((p + 31) / 32);
+  if (blocks < 1 || blocks > INT32_MAX) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_moments_out, dim3((unsigned)blocks), dim3(256), 0, st, moments, p, sp, s, out);
+  return hipGetLastError();
+}
+
 }  // namespace rfo

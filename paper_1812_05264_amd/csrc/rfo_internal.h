@@ -178,6 +178,8 @@ inline int traces_parts(int64_t p) { return (int)std::min<int64_t>(256, (p + 3) 
 hipError_t launch_traces(const double *moments, const double *w,
                          const double *coef, int64_t p, int sp, double *part, double *out3,
                          hipStream_t s);
+// moments [p][sp] -> out [s][p]
+hipError_t launch_moments_out(const double *moments, int64_t p, int sp, int64_t s, double *out, hipStream_t st);
 // Masked outer products on the block pattern:
 //   G[nz] (+)= sum_t coef_t sum_c w_c X_t[I-block][c] Y_t[J-block][c]
 // X_t = xbase + t*xstride (precision-typed), Y_t = ybase + t*ystride, or the
