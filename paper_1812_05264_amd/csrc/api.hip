@@ -550,7 +550,7 @@ int rfo_traces_at(rfo_ctx *ctx, double T, double mu, double *NEF_out) {
   if (!std::isfinite(mu)) return fail(ctx, RFO_E_INVALID, "mu must be finite");
   HIPCHK(hipSetDevice(ctx->device));
   const int64_t p = ctx->mom_p, nq = 4 * p;
-  HIPCHK(rfo::launch_coefficients(ctx->e_min, ctx->e_max, T, mu, p, nq, P<double>(ctx->samples),
+  HIPCHK(rfo::launch_coefficients(ctx->e_min, ctx->e_max, T, mu, p, nq, !is_bf16(ctx->prec), P<double>(ctx->samples),
                                   P<double>(ctx->costab), P<double>(ctx->coef), ctx->stream));
   double *obs = P<double>(ctx->small);
   HIPCHK(rfo::launch_traces(P<double>(ctx->moments), P<double>(ctx->w), P<double>(ctx->coef), p,

@@ -720,7 +720,7 @@ inline int prepare_call(rfo_ctx *ctx, double T, double mu, int64_t p, Plan &pl) 
   TRY(ensure(ctx, ctx->costab, (size_t)4 * nq * sizeof(double)));
   TRY(ensure(ctx, ctx->small, 64 * sizeof(double)));
   HIPCHK(hipMemsetAsync(ctx->flags.p, 0, sizeof(int), ctx->stream));
-  HIPCHK(rfo::launch_coefficients(ctx->e_min, ctx->e_max, T, mu, p, nq, P<double>(ctx->samples),
+  HIPCHK(rfo::launch_coefficients(ctx->e_min, ctx->e_max, T, mu, p, nq, !is_bf16(ctx->prec), P<double>(ctx->samples),
                                   P<double>(ctx->costab), P<double>(ctx->coef), ctx->stream));
   return RFO_OK;
 }

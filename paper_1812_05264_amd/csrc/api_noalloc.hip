@@ -124,7 +124,7 @@ int rfo_fermi_moments_noalloc(rfo_ctx *ctx, double T, double mu, int64_t n_terms
 
   k_clear_flag<<<1, 64, 0, ctx->stream>>>(P<int>(ctx->flags));
   HIPCHK(hipGetLastError());
-  HIPCHK(rfo::launch_coefficients(ctx->e_min, ctx->e_max, T, mu, p, nq, P<double>(ctx->samples),
+  HIPCHK(rfo::launch_coefficients(ctx->e_min, ctx->e_max, T, mu, p, nq, !is_bf16(ctx->prec), P<double>(ctx->samples),
                                   P<double>(ctx->costab), P<double>(ctx->coef), ctx->stream));
   size_t n_events = 0;
   TRY(run_forward(ctx, pl, p, ctx->vec, false, nullptr, &n_events, ctx->doubling));

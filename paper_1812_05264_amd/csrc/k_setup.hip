@@ -172,18 +172,25 @@ hipError_t launch_probe_pack(const double *rden, int64_t n, int s_real, int sp, 
 // entry (k (2j + 1)) mod 4 nq, so the argument reduction is exact for every k.
 // Node nq - 1 - j has the cosine of node j times (-1)^k, so the sums run over half the nodes: the
 // samples are kept as h_j + h_{nq-1-j} (even k, first nq/2 of nq) and h_j - h_{nq-1-j} (odd k).
+//
+// HALF = false, for the BF16 steps: all nodes in order, and the whole turn as the table (4 nq entries).
+// The two ways round differently in the last bit, which means nothing to FP64 and FP32 vectors. The BF16
+// gradient rounds z_j to eight bits in every step, and a last bit in its sources decides some of those
+// roundings: it moved the forces by the path's whole error (1.1e-3 at 16,000 atoms, 1,000 terms). Their
+// coefficients therefore keep one order of sums for good; the call has milliseconds for the 12 us more.
+template <bool HALF>
 __global__ __launch_bounds__(kWG) void k_coef_samples(double e_min, double e_max, double T,
                                                       double mu, int64_t nq,
                                                       double *__restrict__ samples,
                                                       double *__restrict__ costab) {
-  const int64_t half = nq / 2;
-  for (int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; m <= nq;
+  const int64_t half = nq / 2, nodes = HALF ? half : nq, entries = HALF ? nq + 1 : 4 * nq;
+  for (int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; m < entries;
        m += (int64_t)gridDim.x * blockDim.x) {
     costab[m] = cospi((double)m / (double)(2 * nq));
-    if (m < half) {
+    if (m < nodes) {
       double h[2][3];
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
+      for (int t = 0; t < (HALF ? 2 : 1); ++t) {
         const int64_t j = t ? nq - 1 - m : m;
         const double x = cos(M_PI * ((double)j + 0.5) / (double)nq);
         const double e = 0.5 * e_min * (1.0 - x) + 0.5 * e_max * (1.0 + x);
@@ -196,8 +203,8 @@ __global__ __launch_bounds__(kWG) void k_coef_samples(double e_min, double e_max
       }
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
-        samples[i * nq + m] = h[0][i] + h[1][i];
-        samples[i * nq + half + m] = h[0][i] - h[1][i];
+        samples[i * nq + m] = HALF ? h[0][i] + h[1][i] : h[0][i];
+        if (HALF) samples[i * nq + half + m] = h[0][i] - h[1][i];
       }
     }
   }
@@ -209,10 +216,11 @@ __global__ __launch_bounds__(kWG) void k_coef_samples(double e_min, double e_max
 // parity, and so has every fold of it into the quarter turn, so every other entry will do.
 // 1,024 terms: 21 us with one k per workgroup and the whole table in memory, 9.7 now; 4,000 terms: 290
 // and 47.
-template <int NTAB, int NTHR>
+template <int NTAB, int NTHR, bool HALF>
 __global__ __launch_bounds__(NTHR) void k_coefs(const double *__restrict__ samples,
                                                 const double *__restrict__ costab, int64_t nq,
                                                 int64_t p, double *__restrict__ coef) {
+  static_assert(HALF || NTAB == 0, "the table in LDS is a quarter turn");
   constexpr int K = 4, W = NTHR / 64;
   // one slot in 33 unused: the lanes of a wave are k entries apart
   __shared__ double tab[NTAB > 0 ? NTAB + NTAB / 32 : 1];
@@ -224,7 +232,7 @@ __global__ __launch_bounds__(NTHR) void k_coefs(const double *__restrict__ sampl
     for (int m = threadIdx.x; 2 * m + odd <= (int)nq; m += NTHR) tab[slot(m)] = costab[2 * m + odd];
     __syncthreads();
   }
-  const uint32_t M = (uint32_t)(4 * nq), half = (uint32_t)(nq / 2), quarter = (uint32_t)nq;
+  const uint32_t M = (uint32_t)(4 * nq), nodes = (uint32_t)(HALF ? nq / 2 : nq), quarter = (uint32_t)nq;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t groups = (p + 7) / 8 * 2;
   for (int64_t g = blockIdx.x; g < groups; g += gridDim.x) {
@@ -236,14 +244,14 @@ __global__ __launch_bounds__(NTHR) void k_coefs(const double *__restrict__ sampl
       at[u] = k * (2 * threadIdx.x + 1) % M;
       by[u] = k * (2 * NTHR) % M;
     }
-    const double *h = samples + ((g & 1) ? half : 0);
+    const double *h = samples + (HALF && (g & 1) ? nodes : 0);
     double s[3][K];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
       for (int u = 0; u < K; ++u) s[i][u] = 0.0;
 #pragma unroll 4
-    for (uint32_t j = threadIdx.x; j < half; j += NTHR) {
+    for (uint32_t j = threadIdx.x; j < nodes; j += NTHR) {
       double hv[3];
 #pragma unroll
       for (int i = 0; i < 3; ++i) hv[i] = h[i * nq + j];
@@ -252,9 +260,12 @@ __global__ __launch_bounds__(NTHR) void k_coefs(const double *__restrict__ sampl
         uint32_t m = at[u];
         const uint32_t next = m + by[u];
         at[u] = min(next, next - M);           // next - M wraps to the top where next < M
-        m = min(m, M - m);                     // cos(-t) = cos t
-        const bool neg = m > quarter;          // cos(pi - t) = -cos t
-        m = min(m, 2 * quarter - m);
+        bool neg = false;
+        if (HALF) {
+          m = min(m, M - m);                   // cos(-t) = cos t
+          neg = m > quarter;                   // cos(pi - t) = -cos t
+          m = min(m, 2 * quarter - m);
+        }
         const double v = NTAB > 0 ? tab[slot(m >> 1)] : costab[m];
         const double cv = neg ? -v : v;
 #pragma unroll
@@ -281,21 +292,26 @@ __global__ __launch_bounds__(NTHR) void k_coefs(const double *__restrict__ sampl
 }
 
 hipError_t launch_coefficients(double e_min, double e_max, double T, double mu, int64_t p,
-                               int64_t nq, double *samples, double *costab, double *coef,
+                               int64_t nq, bool half, double *samples, double *costab, double *coef,
                                hipStream_t s) {
   if (nq % 2 != 0 || nq < 2 || p > (1 << 20)) return hipErrorInvalidValue;
-  int64_t blocks = (nq + kWG) / kWG;
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(k_coef_samples, dim3((unsigned)blocks), dim3(kWG), 0, s, e_min, e_max, T,
-                     mu, nq, samples, costab);
+  const int64_t blocks = std::min<int64_t>(65536, ((half ? nq + 1 : 4 * nq) + kWG - 1) / kWG);
   const unsigned groups = (unsigned)((p + 7) / 8 * 2);
+  if (!half) {
+    hipLaunchKernelGGL(k_coef_samples<false>, dim3((unsigned)blocks), dim3(kWG), 0, s, e_min, e_max, T, mu, nq, samples,
+                       costab);
+    hipLaunchKernelGGL((k_coefs<0, 256, false>), dim3(groups), dim3(256), 0, s, samples, costab, nq, p, coef);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(k_coef_samples<true>, dim3((unsigned)blocks), dim3(kWG), 0, s, e_min, e_max, T, mu, nq, samples,
+                     costab);
   if (nq <= 8192)  // 32 KB of LDS: several workgroups per compute unit
-    hipLaunchKernelGGL((k_coefs<4097, 256>), dim3(groups), dim3(256), 0, s, samples, costab, nq, p, coef);
+    hipLaunchKernelGGL((k_coefs<4097, 256, true>), dim3(groups), dim3(256), 0, s, samples, costab, nq, p, coef);
   else if (nq <= 32768)  // 128 KB: one, which keeps its table for all its k
-    hipLaunchKernelGGL((k_coefs<16385, 1024>), dim3(std::min(groups, 256u)), dim3(1024), 0, s, samples, costab, nq, p,
+    hipLaunchKernelGGL((k_coefs<16385, 1024, true>), dim3(std::min(groups, 256u)), dim3(1024), 0, s, samples, costab, nq, p,
                        coef);
   else
-    hipLaunchKernelGGL((k_coefs<0, 1024>), dim3(groups), dim3(1024), 0, s, samples, costab, nq, p, coef);
+    hipLaunchKernelGGL((k_coefs<0, 1024, true>), dim3(groups), dim3(1024), 0, s, samples, costab, nq, p, coef);
   return hipGetLastError();
 }
 

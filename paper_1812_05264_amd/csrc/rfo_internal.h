@@ -159,9 +159,10 @@ hipError_t launch_gershgorin(const double *h, const int64_t *row_ptr,
 // Probe classification (all +-1?) and packing to sign bits.
 hipError_t launch_probe_pack(const double *rden, int64_t n, int s_real, int sp,
                              uint64_t *sgn, int *flags, hipStream_t st);
-// Chebyshev coefficients of f, x f, g by Chebyshev-Gauss quadrature over nq nodes (even).
+// Chebyshev coefficients of f, x f, g by Chebyshev-Gauss quadrature over nq nodes (even); samples:
+// 3 nq doubles, costab: nq + 1 with half (node pairs summed first), 4 nq without (BF16 steps).
 hipError_t launch_coefficients(double e_min, double e_max, double T, double mu,
-                               int64_t p, int64_t nq, double *samples,
+                               int64_t p, int64_t nq, bool half, double *samples,
                                double *costab, double *coef, hipStream_t s);
 // Fixed-order reduction of moment partials: moments[k][c] for k in
 // [k0, k0 + count), ring slot of index k is k % ring.  Flags a moment that
