@@ -391,6 +391,9 @@ int rfo_set_moment_doubling(rfo_ctx *ctx, int enabled);
  *                           memory budget above, the last vectors of its forward pass, so the
  *                           top checkpoint segments are not replayed (the same gradient, bitwise;
  *                           the context then holds up to the whole budget).  0 (default)
+ * Small matrices of 1x1 blocks run all steps of rfo_fermi_moments in one launch, which has none of the step
+ * kernels' geometry: setting RFO_TUNE_PPL, _RPI, _ROWS_PER_WG, _GRID or _ALT_SWEEP, also to the value of its
+ * default, makes them run a launch per step.
  * Geometry changes only the order of FP64 sums (rounding).  The segment gradient's step
  * groups, its matrix-core switch and the adjoint's probe batches change how G is summed
  * and so its rounding (and, for RFO_TUNE_SDDMM_MFMA = 0, which operands the BF16

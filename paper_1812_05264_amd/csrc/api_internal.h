@@ -536,6 +536,9 @@ inline int cg_solve(rfo_ctx *ctx, const Plan &pl, DevBuf &bufs, const void *y, v
 inline bool run_resident(const rfo_ctx *ctx, bool use_acc) {
   if (ctx->bd != 1 || ctx->has_s || ctx->run_slices == 0) return false;
   if (ctx->prec == RFO_FP32 && !ctx->signs && use_acc) return false;
+  // a caller who sets the geometry or the sweep of the step kernels gets the step kernels
+  for (int key : {RFO_TUNE_PPL, RFO_TUNE_RPI, RFO_TUNE_ROWS_PER_WG, RFO_TUNE_GRID, RFO_TUNE_ALT_SWEEP})
+    if (ctx->tune[key] >= 0) return false;
   // many rows on few compute units: a launch per step spreads them better (FP32, us one launch / one per step:
   // 10,648 rows and 64 probes 876 / 988, 12,167 and 10 2,135 / 1,929, 13,824 and 64 1,119 / 1,070, 17,576 and
   // 128 1,372 / 1,400)
