@@ -213,6 +213,9 @@ int rfo_set_hamiltonian(rfo_ctx *ctx, int64_t n_block_rows, int block_dim, const
       ctx->run_ns = ns;
       ctx->run_pairs = slice.back();
       ctx->run_max = (int)((ctx->max_row + 1) / 2);
+      int64_t far = 0;
+      for (int64_t z = 0; z < nnzb; ++z) far += 8 * std::abs(brow[z] - col_idx[z]) > nb;
+      ctx->run_far = (double)far / (double)nnzb;
     }
     HIPCHK(hipStreamSynchronize(ctx->stream));  // host vectors go out of scope
   }

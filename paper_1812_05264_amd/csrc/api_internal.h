@@ -49,6 +49,7 @@ struct rfo_ctx {
   DevBuf run_slice, run_perm, run_cols, run_src, run_vals;
   int run_ns = 0, run_slices = 0;  // slices of the pattern; 0 where the steps run one by one
   int run_pairs = 0, run_max = 0;  // entry pairs, and of the widest slice
+  double run_far = 0.0;            // share of the entries more than an eighth of the rows from the diagonal
   // BF16 steps: K chunks of 16 rows per block row (first chunk of each row,
   // gathered row J*9 + c and source nz*9 + c of every K row)
   DevBuf kc_ptr, kc_idx, kc_src;
@@ -531,6 +532,41 @@ inline int cg_solve(rfo_ctx *ctx, const Plan &pl, DevBuf &bufs, const void *y, v
               max_it);
 }
 
+// Time of a step of 1x1 blocks, us: in the one launch of all steps (k_run1), and as a launch of its own
+// (k_step1).  In the one launch a workgroup per column streams the whole matrix from the L2 in every step, 13
+// entries a ns (10.5 where they pass its 4 MB; twice as many from registers), and the columns take
+// turns on the compute units.  The launch per step spreads the rows over the chip and reads the entries once
+// per probe tile, but waits for each row's chain of entries, and gathers a vector row per entry: at 21 TB/s
+// while the XCD's L2 holds the tile's rows that they meet, more slowly where far entries meet more than
+// 5,632 rows of 1 KB.  Measured (us per step, one launch / launch each; rows x entries a row, probes):
+//   FP64  2,000 x 7, 64     1.6 / 6.0   2,000 x 127, 64  21 / 25      5,000 x 15, 64   8.0 / 9.3
+//         5,000 x 31, 64   13.8 / 13.0  5,000 x 127, 64  56 / 36      9,600 x 7, 64    7.7 / 8.9
+//         9,600 x 15, 64   13.3 / 11.8  9,600 x 127, 64 104 / 51      9,600 x 127, 256 106 / 107
+//   FP32  9,600 x 15, 64   13.4 / 10.7  9,600 x 127, 256 100 / 60     9,600 x 15, 512  26.5 / 22.5
+// with neighbouring columns, and with random ones
+//   FP64  9,600 x 127, 64  137 / 87     9,600 x 127, 256 140 / 242
+//   FP32  9,600 x 8, 64    8.4 / 11.8   9,600 x 32, 64   26 / 20      9,600 x 32, 512  51 / 65
+//         16,000 x 8, 128  12.1 / 14.9  16,000 x 32, 128 41 / 32.
+// Over 2,422 calls of 512 to 19,200 rows, 3 to 128 entries a row and 1 to 512 probes, 963 of them sizes that
+// nothing was fitted to, the path taken was at most 11 % slower than the other in all but 16, 28 % in the worst.
+inline double run_us(const rfo_ctx *c, int mode) {
+  const int vt = c->prec == RFO_FP64 ? 8 : 4;
+  const double slots = 128.0 * c->run_pairs, n = (double)c->n;
+  double us = slots / (slots * (vt + 2) > (4 << 20) ? 10500 : 13000);
+  if (rfo::run_held(vt, mode, c->run_slices, c->run_max) > 0) us *= 0.5;
+  if (mode == 1) us += 1e-4 * n;                  // accumulator
+  if (mode != 2 && !c->signs) us += 1.5e-4 * n;   // probes
+  return (double)((c->s + c->cus - 1) / c->cus) * (1.5 + us);
+}
+inline double step_us(const rfo_ctx *c) {
+  const int vt = c->prec == RFO_FP64 ? 8 : 4;
+  const double n = (double)c->n, entries = (double)c->nnzb, row = (double)c->sp * vt, far = c->run_far;
+  const double chain = 0.5 * (entries / n + (double)c->max_row);
+  const double wait = (vt == 8 ? 1.0 : 0.9) * (1.0 + 0.15 * far) * (4.7 + 2e-4 * n + chain * (0.105 + 2.5e-5 * n));
+  const double gather = (entries + 8.0 * n) * row / 21e6 * (1.0 - far + far * std::max(1.0, n / 5632.0));
+  return wait + 0.7 * std::max(0.0, 1.0 - 512.0 / row) * gather;
+}
+
 // The whole forward pass in one launch.  FP32 with dense probes and a density goes step by step: the
 // probes in FP64 and the accumulator do not both fit the two vector slots that serve as work memory.
 inline bool run_resident(const rfo_ctx *ctx, bool use_acc) {
@@ -539,11 +575,7 @@ inline bool run_resident(const rfo_ctx *ctx, bool use_acc) {
   // a caller who sets the geometry or the sweep of the step kernels gets the step kernels
   for (int key : {RFO_TUNE_PPL, RFO_TUNE_RPI, RFO_TUNE_ROWS_PER_WG, RFO_TUNE_GRID, RFO_TUNE_ALT_SWEEP})
     if (ctx->tune[key] >= 0) return false;
-  // many rows on few compute units: a launch per step spreads them better (FP32, us one launch / one per step:
-  // 10,648 rows and 64 probes 876 / 988, 12,167 and 10 2,135 / 1,929, 13,824 and 64 1,119 / 1,070, 17,576 and
-  // 128 1,372 / 1,400)
-  if (ctx->n > 11264 && ctx->s < 128) return false;
-  return true;
+  return run_us(ctx, use_acc ? 1 : ctx->doubling ? 2 : 0) <= step_us(ctx);
 }
 
 inline int run_forward(rfo_ctx *ctx, const Plan &pl, int64_t p, DevBuf &bufs, bool use_acc,

@@ -274,28 +274,26 @@ hipError_t launch_run_fill(int precision, const void *h, const int32_t *src, int
 namespace {
 
 template <typename VT, int MODE>
-const void *run_fn(int waves, int slices, int pairs) {
-  const int rj = (slices + waves - 1) / waves;
+const void *run_fn(int slices, int pairs) {
+  const int rj = run_held(sizeof(VT), MODE, slices, pairs);
   constexpr bool kFull = sizeof(VT) == 8 && MODE != 2;  // 16 pairs beside their other values would spill
-  if (pairs <= 4) {
-    if (rj <= 1) return (const void *)k_run1<VT, MODE, 1, 4>;
-    if (rj <= 2) return (const void *)k_run1<VT, MODE, 2, 4>;
-    if constexpr (!kFull)
-      if (rj <= 4) return (const void *)k_run1<VT, MODE, 4, 4>;
-  } else if (pairs <= 8) {
-    if (rj <= 1) return (const void *)k_run1<VT, MODE, 1, 8>;
-    if constexpr (!kFull)
-      if (rj <= 2) return (const void *)k_run1<VT, MODE, 2, 8>;
+  if (rj > 0 && pairs <= 4) {
+    if (rj == 1) return (const void *)k_run1<VT, MODE, 1, 4>;
+    if (rj == 2) return (const void *)k_run1<VT, MODE, 2, 4>;
+    if constexpr (!kFull) return (const void *)k_run1<VT, MODE, 4, 4>;
+  } else if (rj > 0) {
+    if (rj == 1) return (const void *)k_run1<VT, MODE, 1, 8>;
+    if constexpr (!kFull) return (const void *)k_run1<VT, MODE, 2, 8>;
   }
   return (const void *)k_run1<VT, MODE, 0, 4>;
 }
 
 template <typename VT>
-const void *run_fn_m(int mode, int waves, int slices, int pairs) {
+const void *run_fn_m(int mode, int slices, int pairs) {
   switch (mode) {
-    case 0: return run_fn<VT, 0>(waves, slices, pairs);
-    case 1: return run_fn<VT, 1>(waves, slices, pairs);
-    default: return run_fn<VT, 2>(waves, slices, pairs);
+    case 0: return run_fn<VT, 0>(slices, pairs);
+    case 1: return run_fn<VT, 1>(slices, pairs);
+    default: return run_fn<VT, 2>(slices, pairs);
   }
 }
 
@@ -305,8 +303,8 @@ hipError_t launch_run(int precision, int mode, int max_pairs, const RunArgs &a, 
   const int64_t vt = precision == 0 ? 8 : 4;
   if (a.n < 1 || a.n > run_rows((int)vt) || a.sp < 1 || (mode == 1 && (!a.acc || !a.work))) return hipErrorInvalidValue;
   const int waves = std::min(kRunWaves, a.n_slices);
-  const void *f = precision == 0 ? run_fn_m<double>(mode, waves, a.n_slices, max_pairs)
-                                 : run_fn_m<float>(mode, waves, a.n_slices, max_pairs);
+  const void *f = precision == 0 ? run_fn_m<double>(mode, a.n_slices, max_pairs)
+                                 : run_fn_m<float>(mode, a.n_slices, max_pairs);
   const int bytes = (int)(2 * vt * a.n);
   // the same value on every call: other threads launch this kernel too
   const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(2 * vt * run_rows((int)vt)));

@@ -103,6 +103,13 @@ struct RunArgs {
   double tol;              // flags bit 2: a moment above (1 + tol) moment 0
   int *flags;
 };
+// Slices that a wave keeps in its registers, 0 where it streams them in every step: those of at most 4 or 8 pairs,
+// as many as fit beside its other values (FP64 that is not doubled: half)
+inline int run_held(int vt_bytes, int mode, int slices, int max_pairs) {
+  const int waves = std::min(kRunWaves, slices), rj = (slices + waves - 1) / waves;
+  const int most = (max_pairs <= 4 ? 4 : max_pairs <= 8 ? 2 : 0) / (vt_bytes == 8 && mode != 2 ? 2 : 1);
+  return rj <= most ? rj : 0;
+}
 // mode 0: moments r . y_k; 1: those and the density accumulator; 2: moments by doubling
 hipError_t launch_run(int precision, int mode, int max_pairs, const RunArgs &a, hipStream_t s);
 // dst[e] = h[src[e]] or zero
