@@ -58,6 +58,52 @@ const char *rfo_last_error(const rfo_ctx *ctx) {
   return ctx ? ctx->err.c_str() : g_create_error.c_str();
 }
 
+// Slices of a small matrix of 1x1 blocks (RunArgs): rows sorted by length (stable), 64 to a slice, a slice as wide as
+// its longest row in pairs of entries.  Built for the first precision whose vectors fit the one launch, once
+// per pattern.
+static int build_slices(rfo_ctx *ctx) {
+  const std::vector<int64_t> &row_ptr = ctx->row_ptr_h;
+  const std::vector<int32_t> &col_idx = ctx->col_h;
+  const int64_t nb = ctx->nb;
+  const int ns = (int)((nb + 63) / 64);
+  std::vector<int64_t> start(ctx->max_row + 2, 0);
+  auto len = [&](int64_t I) { return row_ptr[I + 1] - row_ptr[I]; };
+  for (int64_t I = 0; I < nb; ++I) ++start[ctx->max_row - len(I) + 1];
+  for (int64_t k = 1; k < (int64_t)start.size(); ++k) start[k] += start[k - 1];
+  std::vector<int32_t> perm((size_t)ns * 64, -1), slice(1, 0);
+  for (int64_t I = 0; I < nb; ++I) perm[start[ctx->max_row - len(I)]++] = (int32_t)I;
+  for (int t = 0; t < ns; ++t) slice.push_back(slice.back() + (int32_t)((len(perm[t * 64]) + 1) / 2));
+  std::vector<int32_t> src((size_t)slice.back() * 128, -1);
+  std::vector<uint32_t> cols((size_t)slice.back() * 64, 0);
+  int64_t far = 0;
+  for (int t = 0; t < ns; ++t)
+    for (int l = 0; l < 64; ++l) {
+      const int32_t I = perm[t * 64 + l];
+      if (I < 0) continue;
+      for (int64_t z = row_ptr[I]; z < row_ptr[I + 1]; ++z) {
+        const int64_t k = z - row_ptr[I], e = ((int64_t)slice[t] + k / 2) * 64 + l;
+        src[2 * e + k % 2] = (int32_t)z;
+        cols[e] |= (uint32_t)col_idx[z] << (16 * (k % 2));
+        far += 8 * (int64_t)std::abs(I - col_idx[z]) > nb;
+      }
+    }
+  auto upload = [&](DevBuf &b, const void *p, size_t bytes) -> int {
+    TRY(ensure(ctx, b, bytes));
+    HIPCHK(hipMemcpyAsync(b.p, p, bytes, hipMemcpyHostToDevice, ctx->stream));
+    return RFO_OK;
+  };
+  TRY(upload(ctx->run_slice, slice.data(), slice.size() * sizeof(int32_t)));
+  TRY(upload(ctx->run_perm, perm.data(), perm.size() * sizeof(int32_t)));
+  TRY(upload(ctx->run_cols, cols.data(), cols.size() * sizeof(uint32_t)));
+  TRY(upload(ctx->run_src, src.data(), src.size() * sizeof(int32_t)));
+  HIPCHK(hipStreamSynchronize(ctx->stream));  // host vectors go out of scope
+  ctx->run_pairs = slice.back();
+  ctx->run_max = (int)((ctx->max_row + 1) / 2);
+  ctx->run_far = (double)far / (double)ctx->nnzb;
+  ctx->run_ns = ns;
+  return RFO_OK;
+}
+
 int rfo_set_hamiltonian(rfo_ctx *ctx, int64_t n_block_rows, int block_dim, const int64_t *row_ptr,
                         const int32_t *col_idx, const double *values, double e_min,
                         double e_max, int precision) {
@@ -124,6 +170,7 @@ int rfo_set_hamiltonian(rfo_ctx *ctx, int64_t n_block_rows, int block_dim, const
     }
     ctx->has_h = false;
     ctx->has_grad = false;
+    ctx->run_ns = 0;
     ctx->nb = nb;
     ctx->bd = block_dim;
     ctx->n = n;
@@ -174,49 +221,6 @@ int rfo_set_hamiltonian(rfo_ctx *ctx, int64_t n_block_rows, int block_dim, const
     ctx->n_grp_up = (int64_t)gu.size() - 1;
     ctx->n_grp_all = (int64_t)ga.size() - 1;
 
-    // small matrices of 1x1 blocks: rows sorted by length (stable) in slices of 64, a slice as wide as
-    // its longest row in pairs of entries
-    ctx->run_ns = 0;
-    std::vector<int32_t> slice, perm, src;
-    std::vector<uint32_t> cols;
-    if (block_dim == 1 && nb <= rfo::run_rows(4)) {
-      const int ns = (int)((nb + 63) / 64);
-      std::vector<int64_t> start(ctx->max_row + 2, 0);
-      auto len = [&](int64_t I) { return row_ptr[I + 1] - row_ptr[I]; };
-      for (int64_t I = 0; I < nb; ++I) ++start[ctx->max_row - len(I) + 1];
-      for (int64_t k = 1; k < (int64_t)start.size(); ++k) start[k] += start[k - 1];
-      perm.assign((size_t)ns * 64, -1);
-      for (int64_t I = 0; I < nb; ++I) perm[start[ctx->max_row - len(I)]++] = (int32_t)I;
-      slice.assign(1, 0);
-      for (int t = 0; t < ns; ++t) slice.push_back(slice.back() + (int32_t)((len(perm[t * 64]) + 1) / 2));
-      src.assign((size_t)slice.back() * 128, -1);
-      cols.assign((size_t)slice.back() * 64, 0);
-      for (int t = 0; t < ns; ++t)
-        for (int l = 0; l < 64; ++l) {
-          const int32_t I = perm[t * 64 + l];
-          if (I < 0) continue;
-          for (int64_t z = row_ptr[I]; z < row_ptr[I + 1]; ++z) {
-            const int64_t k = z - row_ptr[I], e = ((int64_t)slice[t] + k / 2) * 64 + l;
-            src[2 * e + k % 2] = (int32_t)z;
-            cols[e] |= (uint32_t)col_idx[z] << (16 * (k % 2));
-          }
-        }
-      auto upload = [&](DevBuf &b, const void *p, size_t bytes) -> int {
-        TRY(ensure(ctx, b, bytes));
-        HIPCHK(hipMemcpyAsync(b.p, p, bytes, hipMemcpyHostToDevice, ctx->stream));
-        return RFO_OK;
-      };
-      TRY(upload(ctx->run_slice, slice.data(), slice.size() * sizeof(int32_t)));
-      TRY(upload(ctx->run_perm, perm.data(), perm.size() * sizeof(int32_t)));
-      TRY(upload(ctx->run_cols, cols.data(), cols.size() * sizeof(uint32_t)));
-      TRY(upload(ctx->run_src, src.data(), src.size() * sizeof(int32_t)));
-      ctx->run_ns = ns;
-      ctx->run_pairs = slice.back();
-      ctx->run_max = (int)((ctx->max_row + 1) / 2);
-      int64_t far = 0;
-      for (int64_t z = 0; z < nnzb; ++z) far += 8 * std::abs(brow[z] - col_idx[z]) > nb;
-      ctx->run_far = (double)far / (double)nnzb;
-    }
     HIPCHK(hipStreamSynchronize(ctx->stream));  // host vectors go out of scope
   }
   ctx->has_h = false;
@@ -303,15 +307,14 @@ int rfo_set_hamiltonian(rfo_ctx *ctx, int64_t n_block_rows, int block_dim, const
                          P<double>(ctx->h64), precision == RFO_FP32 ? P<float>(ctx->h32) : nullptr,
                          P<int>(ctx->flags), ctx->stream));
   ctx->run_slices = 0;
-  if (ctx->run_ns > 0 && !is_bf16(precision)) {
-    const int vt = precision == RFO_FP64 ? 8 : 4;
-    if (ctx->nb <= rfo::run_rows(vt)) {
-      TRY(ensure(ctx, ctx->run_vals, (size_t)ctx->run_pairs * 128 * vt));
-      HIPCHK(rfo::launch_run_fill(kernel_precision(ctx), precision == RFO_FP64 ? ctx->h64.p : ctx->h32.p,
-                                  P<int32_t>(ctx->run_src), (int64_t)ctx->run_pairs * 128, ctx->run_vals.p,
-                                  ctx->stream));
-      ctx->run_slices = ctx->run_ns;
-    }
+  const int vt = precision == RFO_FP64 ? 8 : 4;
+  if (ctx->bd == 1 && ctx->nb <= rfo::run_rows(vt)) {
+    if (ctx->run_ns == 0) TRY(build_slices(ctx));
+    TRY(ensure(ctx, ctx->run_vals, (size_t)ctx->run_pairs * 128 * vt));
+    HIPCHK(rfo::launch_run_fill(kernel_precision(ctx), precision == RFO_FP64 ? ctx->h64.p : ctx->h32.p,
+                                P<int32_t>(ctx->run_src), (int64_t)ctx->run_pairs * 128, ctx->run_vals.p,
+                                ctx->stream));
+    ctx->run_slices = ctx->run_ns;
   }
   if (is_bf16(precision))
     HIPCHK(rfo::launch_pack_bf16(P<double>(ctx->h64), P<int32_t>(ctx->kc_src), ctx->n_chunks,

@@ -47,7 +47,7 @@ struct rfo_ctx {
   // small matrices of 1x1 blocks: rows sorted by length in slices of 64 (RunArgs), the nonzero of each
   // slot and the values in the precision of the steps
   DevBuf run_slice, run_perm, run_cols, run_src, run_vals;
-  int run_ns = 0, run_slices = 0;  // slices of the pattern; 0 where the steps run one by one
+  int run_ns = 0, run_slices = 0;  // slices built for the pattern, and usable in the set precision (0: none)
   int run_pairs = 0, run_max = 0;  // entry pairs, and of the widest slice
   double run_far = 0.0;            // share of the entries more than an eighth of the rows from the diagonal
   // BF16 steps: K chunks of 16 rows per block row (first chunk of each row,

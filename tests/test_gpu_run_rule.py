@@ -97,3 +97,37 @@ def test_largest_that_fit(s, n, prec, path, dense):
         else:
             assert np.max(np.abs(m - o["moments"]) / o["moments"][:, :1]) < bound
     assert np.max(np.abs(d["density"] - o["density"])) < bound * np.max(np.abs(o["density"]))
+
+
+def test_slices_are_built_for_a_precision_that_runs_them():
+    """FP64 keeps no second copy of a pattern whose vectors do not fit the one launch: the device memory of a
+    Hamiltonian of 11.6M entries is its values twice (16 bytes an entry), columns, block rows, mirror and list
+    positions (28), allocated in units of 2 MiB. The kept pattern set in FP32 builds the slices then, and back in FP64
+    goes without them."""
+    banner("slices by precision")
+    import torch
+    n, entries = 9700, 1201
+    H = band(n, entries)
+    eng = engine_or_skip()
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    eng.set_hamiltonian(H.row_ptr, H.col_idx, H.values, 1, H.e_min, H.e_max, "fp64")
+    used = before - torch.cuda.mem_get_info()[0]
+    print(f"{used / H.nnzb:.1f} bytes an entry")
+    assert used < 44 * H.nnzb + 12 * (2 << 20)
+    H = band(n, 5)
+    R = rademacher(n, 3, config_id=67)
+    o = est.estimate(H, R, T, MU, P, density=True)
+    bound = 2.0 * P ** 2 * 10 * 2.0 ** -24
+    eng.set_hamiltonian(H.row_ptr, H.col_idx, H.values, 1, H.e_min, H.e_max, "fp64")
+    eng.set_probes(R)
+    check_moments(eng.fermi_moments(T, MU, P, moments=True)["moments"], o["moments"])
+    eng.set_hamiltonian(None, None, H.values, 1, H.e_min, H.e_max, "fp32")
+    one = eng.fermi_moments(T, MU, P, moments=True)["moments"]
+    eng.set_tuning("alt_sweep", 1)
+    steps = eng.fermi_moments(T, MU, P, moments=True)["moments"]
+    eng.set_tuning("alt_sweep", -1)
+    assert not np.array_equal(one, steps)
+    assert np.max(np.abs(one - o["moments"]) / o["moments"][:, :1]) < bound
+    eng.set_hamiltonian(None, None, H.values, 1, H.e_min, H.e_max, "fp64")
+    check_moments(eng.fermi_moments(T, MU, P, moments=True)["moments"], o["moments"])
