@@ -1,7 +1,8 @@
 """Small matrices of 1x1 blocks, all steps in one launch: row counts beside the slices of 64 and the
-workgroup's 16 waves, rows short enough for the registers and not, the largest matrices that fit and the
-first that do not, both precisions, sign-bit and dense probes, moments (doubled and direct) and
-density, against the oracle.
+workgroup's 16 waves, rows short enough for the registers and not, both precisions, sign-bit and dense
+probes, moments (doubled and direct) and density, against the oracle.  Graphs of 9,600 rows and more have
+so many entries that they take a launch per step; test_gpu_run_rule.py has the largest matrices that run in one
+and the first whose vectors do not fit.
 
 Bounds as in the tests of the 9x9 step, with b entries in a row: a moment of p terms is off by at most
 4 p^2/2 (b + 5) u || |H_hat| ||_inf ||r||^2, and so is the density, in units of its largest entry (an
