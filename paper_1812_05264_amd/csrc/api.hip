@@ -175,10 +175,9 @@ int rfo_set_hamiltonian(rfo_ctx *ctx, int64_t n_block_rows, int block_dim, const
     ctx->bd = block_dim;
     ctx->n = n;
     ctx->nnzb = nnzb;
-    ctx->row_ptr_h.assign(row_ptr, row_ptr + nb + 1);
+    ctx->row_ptr_h.clear();  // the pattern can be kept once all of it is there
     ctx->max_row = 0;
     for (int64_t I = 0; I < nb; ++I) ctx->max_row = std::max(ctx->max_row, row_ptr[I + 1] - row_ptr[I]);
-    ctx->col_h.assign(col_idx, col_idx + nnzb);
     TRY(ensure(ctx, ctx->row_ptr, (nb + 1) * sizeof(int64_t)));
     TRY(ensure(ctx, ctx->col, (nnzb + rfo::kStepPad) * sizeof(int32_t)));
     TRY(ensure(ctx, ctx->brow, nnzb * sizeof(int64_t)));
@@ -222,6 +221,8 @@ int rfo_set_hamiltonian(rfo_ctx *ctx, int64_t n_block_rows, int block_dim, const
     ctx->n_grp_all = (int64_t)ga.size() - 1;
 
     HIPCHK(hipStreamSynchronize(ctx->stream));  // host vectors go out of scope
+    ctx->col_h.assign(col_idx, col_idx + nnzb);
+    ctx->row_ptr_h.assign(row_ptr, row_ptr + nb + 1);
   }
   ctx->has_h = false;
   ctx->has_grad = false;
