@@ -86,19 +86,25 @@ int rfo_fermi_moments_noalloc(rfo_ctx *ctx, double T, double mu, int64_t n_terms
   TRY(validate_call(ctx, T, mu, n_terms));
   if (ctx->has_s)
     return fail(ctx, RFO_E_UNSUPPORTED, "the allocation-free call does not take an overlap");
-  const Plan pl = make_plan(ctx);
+  Plan pl = make_plan(ctx);
   const int64_t p = n_terms, nq = 4 * p;
   const size_t sp = (size_t)ctx->sp;
   // regions of the scratch array, each 256-byte aligned
   const size_t sz_vec = round256(2 * pl.slot_bytes);
-  const size_t sz_ring = round256((size_t)pl.ring * pl.grid * sp * sizeof(double));
   const size_t sz_mom = round256((size_t)p * sp * sizeof(double));
   const size_t sz_coef = round256((size_t)3 * p * sizeof(double));
   const size_t sz_samp = round256((size_t)3 * nq * sizeof(double));
   const size_t sz_cos = round256((size_t)4 * nq * sizeof(double));
   const size_t sz_small = round256(64 * sizeof(double));
   const size_t sz_out = round256((size_t)ctx->s * p * sizeof(double));
-  const size_t need = sz_vec + sz_ring + sz_mom + sz_coef + sz_samp + sz_cos + sz_small + sz_out;
+  const size_t rest = sz_vec + sz_mom + sz_coef + sz_samp + sz_cos + sz_small + sz_out;
+  // A ring of fewer moments where 32 do not fit: shorter batches of the same reductions, so the same moments.
+  // (A moment's partials are 8 bytes per probe and workgroup; 9x9 steps of many probes on few block rows take
+  // up to four times the workgroups that one tile of 128 columns per workgroup had: 55 block rows, 1,024 probes
+  // 448 and 112, 117 MB of the 134.)
+  auto ring_bytes = [&]() { return round256((size_t)pl.ring * pl.grid * sp * sizeof(double)); };
+  while (pl.ring > 4 && rest + ring_bytes() > kScratchBytes) pl.ring /= 2;
+  const size_t sz_ring = ring_bytes(), need = rest + sz_ring;
   if (need > kScratchBytes)
     return fail(ctx, RFO_E_INVALID,
                 "this call needs %zu bytes of work memory; the allocation-free call has %zu "
