@@ -159,8 +159,8 @@ int rfo_fermi_moments(rfo_ctx *ctx, double T, double mu, int64_t n_terms,
  * every call on that device: calls that overlap on one device race.  It must
  * hold two probe vectors (n * sp * 8 bytes each in FP64; 4 in FP32; 6 in BF16,
  * sp = s rounded up to 64, or to 128 above 64 probes), the moment partials and
- * moments, the coefficient tables (about 270 * n_terms bytes) and the moments in
- * the caller's layout (s * n_terms * 8 bytes).
+ * moments, the coefficient tables (about 150 * n_terms bytes, 250 in BF16) and
+ * the moments in the caller's layout (s * n_terms * 8 bytes).
  *   moments_out [s][p], NEF_out [3]: as for rfo_fermi_moments (nullable; host
  *   or device memory).
  * H and probes are those of the last rfo_set_hamiltonian / rfo_set_probes.

@@ -184,6 +184,9 @@ inline int64_t tuned(const rfo_ctx *c, int key, int64_t def) {
 
 inline int kernel_precision(const rfo_ctx *c) { return c->prec == RFO_FP64 ? 0 : 1; }
 
+// entries of the cosine table of launch_coefficients
+inline int64_t costab_entries(const rfo_ctx *c, int64_t nq) { return is_bf16(c->prec) ? 4 * nq : nq + 1; }
+
 template <typename T>
 T *P(DevBuf &b) {
   return static_cast<T *>(b.p);
@@ -752,7 +755,7 @@ inline int prepare_call(rfo_ctx *ctx, double T, double mu, int64_t p, Plan &pl) 
   TRY(ensure(ctx, ctx->moments, (size_t)p * ctx->sp * sizeof(double)));
   TRY(ensure(ctx, ctx->coef, (size_t)3 * p * sizeof(double)));
   TRY(ensure(ctx, ctx->samples, (size_t)3 * nq * sizeof(double)));
-  TRY(ensure(ctx, ctx->costab, (size_t)4 * nq * sizeof(double)));
+  TRY(ensure(ctx, ctx->costab, (size_t)costab_entries(ctx, nq) * sizeof(double)));
   TRY(ensure(ctx, ctx->small, 64 * sizeof(double)));
   HIPCHK(hipMemsetAsync(ctx->flags.p, 0, sizeof(int), ctx->stream));
   HIPCHK(rfo::launch_coefficients(ctx->e_min, ctx->e_max, T, mu, p, nq, !is_bf16(ctx->prec), P<double>(ctx->samples),

@@ -94,7 +94,7 @@ int rfo_fermi_moments_noalloc(rfo_ctx *ctx, double T, double mu, int64_t n_terms
   const size_t sz_mom = round256((size_t)p * sp * sizeof(double));
   const size_t sz_coef = round256((size_t)3 * p * sizeof(double));
   const size_t sz_samp = round256((size_t)3 * nq * sizeof(double));
-  const size_t sz_cos = round256((size_t)4 * nq * sizeof(double));
+  const size_t sz_cos = round256((size_t)costab_entries(ctx, nq) * sizeof(double));
   const size_t sz_small = round256(64 * sizeof(double));
   const size_t sz_out = round256((size_t)ctx->s * p * sizeof(double));
   const size_t rest = sz_vec + sz_mom + sz_coef + sz_samp + sz_cos + sz_small + sz_out;

@@ -16,7 +16,7 @@ struct CxWork {
   double *x, *r, *p, *q, *s;  // complex: two planes each
   double *acc;                // real plane: P r accumulator
   double *part, *part2;       // column partials
-  double *sc;                 // CGLS scalars [7][sp] + resmax
+  double *sc;                 // CGLS scalars [8][sp] + resmax
   int nparts;                 // rows of part / part2
   int ppl;                    // complex product, 1x1: probes per lane; 9x9: column tiles per wave
   int u;                      // 1x1: neighbours per chunk

@@ -239,7 +239,6 @@ constexpr int kSddmmGroup = 6;  // measured best (10: 22% slower)
 struct SddmmMfmaArgs {
   const int64_t *grp;      // [n_grp + 1]
   int64_t n_grp;
-  int spread;              // 9x9, set by the launch: items take their probes over several steps
   const int64_t *nzlist;
   const int64_t *brow;
   const int32_t *col;
