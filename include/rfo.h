@@ -191,9 +191,9 @@ int rfo_traces_at(rfo_ctx *ctx, double T, double mu, double *NEF_out);
  *   dFdH_out  [nnzb][bd][bd]  raw gradient G (nullable)
  * The gradient also stays on the device for rfo_hf_forces.
  * Probe columns run in batches, each adding its sums to G, when the vectors of all
- * probes exceed the memory budget (RFO_TUNE_ADJOINT_BYTES), and, in FP64 and FP32, when
- * the last probe tile of 128 columns holds at most 64 real ones (that tile then runs
- * 64 columns wide); batches change only the order of the FP64 sums.
+ * probes exceed the memory budget (RFO_TUNE_ADJOINT_BYTES), and, for 1x1 blocks and for
+ * large 9x9 FP64 vectors, when the last probe tile of 128 columns holds at most 64 real
+ * ones (that tile then runs 64 columns wide); batches change only the order of the FP64 sums.
  * With an overlap S (rfo_set_overlap) the derivative is that of F~ = sum_k beta_k
  * r^T T_k(H_hat S^{-1}) r (paper: Eq. polynomial_response), taken by the direct
  * recurrence (no moment doubling) with one conjugate-gradient solve per forward,

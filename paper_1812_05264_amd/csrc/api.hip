@@ -495,9 +495,9 @@ int rfo_fermi_moments(rfo_ctx *ctx, double T, double mu, int64_t n_terms, double
   ctx->err.clear();
   Plan pl;
   TRY(prepare_call(ctx, T, mu, n_terms, pl));
-  // a last probe tile of 128 columns with at most 64 real probes runs as a batch
+  // a last probe tile of 128 columns with at most 64 real probes may run as a batch
   // of its own, 64 columns wide
-  const auto batches = last_tile_batches(ctx);
+  const auto batches = last_tile_batches(ctx, density_out != nullptr);
   if (!batches.empty() && !run_resident(ctx, density_out != nullptr)) return fermi_moments_batches(ctx, n_terms, batches, moments_out, NEF_out, density_out);
   const bool dens = density_out != nullptr;
   // vector slots: y pair; with an overlap also t and the CG vectors r, p, q

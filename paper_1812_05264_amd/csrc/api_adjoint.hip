@@ -611,13 +611,12 @@ int rfo_energy_and_dEdH(rfo_ctx *ctx, double T, double mu, int64_t n_terms, doub
   double *obs = P<double>(ctx->small);
   // Probe batches [c0, c0 + s_b): of `width` columns when the budget asks for them.
   // Without that, a last probe tile of 128 columns holding at most 64 real ones
-  // runs as a batch of its own, 64 columns wide: a tile costs about the same whatever
-  // part of it is live (the Hamiltonian is read and staged once per tile).
+  // may run as a batch of its own, 64 columns wide (last_tile_batches).
   std::vector<std::pair<int64_t, int64_t>> batches;
   if (width < ctx->sp) {
     for (int64_t c0 = 0; c0 < ctx->s; c0 += width) batches.push_back({c0, std::min<int64_t>(width, ctx->s - c0)});
   } else {
-    batches = last_tile_batches(ctx);
+    batches = last_tile_batches(ctx, true);
   }
   if (batches.empty()) {
     const size_t need = adjoint_slot_bytes(ctx, pl, p, dbl);

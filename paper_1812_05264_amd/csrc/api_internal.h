@@ -835,13 +835,20 @@ struct ProbeBatches {
 // A last probe tile of 128 columns that holds at most 64 real probes runs as a batch of its own,
 // 64 columns wide: the batches [0, s - r), [s - r, s), or none.  1x1: a tile costs about the same
 // whatever part of it is live.  9x9: the tiles are narrower, and the batches pay only by the rows that
-// they keep out of the caches at a time (gradient, ms with and without: 16,000 atoms FP64, 140 probes
-// 45.7 and 53.6; 4,000 FP32, 288 probes 22.1 and 27.7; 6,000 FP32, 150 probes 20.5 and 19.8; 1,000 FP64,
-// 130 probes 6.2 and 5.6; 1,000 FP32, 190 probes 5.7 and 4.4): vectors under 16 MiB run whole.
-inline std::vector<std::pair<int64_t, int64_t>> last_tile_batches(const rfo_ctx *c) {
+// they keep out of the caches at a time: vectors of 128 MiB and more, and in FP32, where the outer products
+// gain nothing by it, moments alone (`blocks`: the call forms density blocks or a gradient).  Whole and in two
+// batches, 50 terms, ms:
+//   FP64 gradient  1,000 atoms, 190 probes 3.20 / 3.83   4,000, 160 10.6 / 10.5   6,000, 320 26.6 / 26.6
+//                  10,000, 257 44.9 / 41.0               16,000, 160 46.0 / 41.4
+//   FP64 moments   1,000, 190 0.72 / 0.93                6,000, 320 5.30 / 5.11   16,000, 160 9.98 / 7.87
+//   FP32 gradient  2,000, 190 4.05 / 4.90                6,000, 150 10.1 / 11.3   16,000, 160 27.8 / 28.3
+//   FP32 moments   2,000, 190 0.88 / 1.10                6,000, 150 2.08 / 2.12   16,000, 160 5.31 / 4.68
+inline std::vector<std::pair<int64_t, int64_t>> last_tile_batches(const rfo_ctx *c, bool blocks) {
   if (c->has_s || is_bf16(c->prec) || c->s <= 128 || c->s % 128 == 0 || c->s % 128 > 64) return {};
-  const int64_t vec = c->nb * c->bd * (int64_t)c->sp * (c->prec == RFO_FP64 ? 8 : 4);
-  if (c->bd == 9 && vec < (int64_t)16 << 20) return {};
+  if (c->bd == 9) {
+    const int64_t vec = c->n * (int64_t)c->sp * (c->prec == RFO_FP64 ? 8 : 4);
+    if (vec < (int64_t)128 << 20 || (blocks && c->prec == RFO_FP32)) return {};
+  }
   const int64_t r = c->s % 128;
   return {{0, c->s - r}, {c->s - r, r}};
 }

@@ -1,8 +1,9 @@
 """A last probe tile of 128 columns with at most 64 real ones as a batch of its own, at sizes that take it: 9x9
-vectors of 16 MiB and more (1,000 block rows, 256 padded columns), and 1x1 matrices too large for the one launch
-of all steps.  Moments, density and gradient, doubled and direct, sign-bit and dense probes with unequal weights,
+FP64 vectors of 128 MiB and more (7,300 block rows, 256 padded columns), and 1x1 matrices too large for the one
+launch of all steps.  Moments, density and gradient, doubled and direct, sign-bit and dense probes with unequal weights,
 against the oracle at the parity bar; the step count of each call shows that it ran as two batches, and the
-moments are bitwise those of a call on each column range.
+moments are bitwise those of a call on each column range.  Smaller 9x9 vectors, and FP32 ones with density or gradient,
+run whole.
 """
 
 import numpy as np
@@ -14,8 +15,8 @@ from workloads import cu_cluster, rademacher, simple_cubic
 
 pytestmark = pytest.mark.gpu
 
-T, MU, P = 0.3, 0.2, 13
-MODELS = {"cu1000": lambda: cu_cluster(1000, config_id=54).bsr(),
+T, MU, P = 0.3, 0.2, 5   # 2 and 4 steps: the sweep alternates, and an even count leaves it forward for the next batch
+MODELS = {"cu7300": lambda: cu_cluster(7300, config_id=54).bsr(),
           "sc22": lambda: simple_cubic(22, disorder=0.5, config_id=54)}
 
 
@@ -28,7 +29,7 @@ def steps_of(eng, call):
 
 
 @pytest.mark.timeout(300)
-@pytest.mark.parametrize("model,dense,s", [("cu1000", False, 160), ("cu1000", True, 150), ("sc22", False, 190),
+@pytest.mark.parametrize("model,dense,s", [("cu7300", False, 160), ("cu7300", True, 150), ("sc22", False, 190),
                                            ("sc22", True, 129)])
 def test_last_tile_batch(model, dense, s):
     banner(f"last-tile batch {model} s={s} dense={dense}")
@@ -65,3 +66,21 @@ def test_last_tile_batch(model, dense, s):
                 check_blocks(g["density"], o["density"], what=name)
             if name == "gradient":
                 check_blocks(g["dFdH"], o["dFdH"], what=name)
+
+
+@pytest.mark.parametrize("prec,atoms,calls", [("fp64", 1000, ("moments", "density", "gradient")),
+                                              ("fp32", 1000, ("moments", "density", "gradient")),
+                                              ("fp32", 14600, ("density", "gradient"))])
+def test_runs_whole(prec, atoms, calls):
+    banner(f"whole last tile {prec} atoms={atoms}")
+    H = cu_cluster(atoms, config_id=55).bsr()
+    R = rademacher(H.n, 150, config_id=905)
+    eng = engine_or_skip()
+    load_hamiltonian(eng, H, precision=prec)
+    run = {"moments": lambda: eng.fermi_moments(T, MU, P, moments=True),
+           "density": lambda: eng.fermi_moments(T, MU, P, moments=False, density=True),
+           "gradient": lambda: eng.energy_and_dEdH(T, MU, P)}
+    eng.set_probes(R[:, :64])
+    one = {k: steps_of(eng, run[k])[1] for k in calls}
+    eng.set_probes(R)
+    assert {k: steps_of(eng, run[k])[1] for k in calls} == one
