@@ -56,7 +56,6 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(NT == 1 && 
   mat[0] = a.hval;
   if constexpr (HS) mat[1] = a.sval;
   const double *const xs[2] = {a.x, a.x + a.plane};
-  const bool live[1] = {true};
   int cur = -1;
   for (Sched sc(a.n_pt / tpw, a.n_rg); sc.more(); sc.next()) {
     const int pg = sc.pt();
@@ -71,7 +70,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(NT == 1 && 
     for (int64_t I = r0 + wr; I < r1; I += kWaves / tpw) {
       const int64_t beg = sld(a.row_ptr + I), end = sld(a.row_ptr + I + 1);
       Prod pr;
-      pr.row(mat, a.col, xs, beg, end, sp * 8, lane, live, Prod::lane_bytes(lane, sp, pt), hw);
+      pr.row(mat, a.col, xs, beg, end, sp * 8, lane, Prod::lane_bytes(lane, sp, pt), hw);
       // one scalar row: si = H_hat x of both planes, m = x or S x
       auto finish = [&](int64_t row, const double(&si)[2][PW], const double(&mi)[2][PW]) {
         const int64_t off = row * sp + c;

@@ -10,6 +10,11 @@
 // at 28 TB/s from an XCD's L2, 7.2 TB/s from beyond it, whatever their shape), which the tile
 // width sets together with the rows in flight: FP64, 256 probes, 16,000 block rows 486 -> 468 us,
 // 6,000 171 -> 154, 4,000 with 128 probes 69 -> 55.
+//
+// Padding columns of a tile are read and computed like the others (dense probes: zeros).  Variants that skipped
+// their loads held a predicate through the product loop and spilled up to 58 registers there: FP32, 100
+// dense probes of 128 columns, 60 terms 1,641 us on 3,000 block rows against 990 without, FP64 1,658 and
+// 1,343; nowhere faster (13 to 12,000 block rows, 1 to 288 probes, all modes: 0.57 to 1.01 of their time).
 #include "moment_flush.h"
 #include "prod9.h"
 
@@ -25,7 +30,7 @@ constexpr int step9_waves() {
 
 }  // namespace
 
-template <typename VT, int NT, int MODE, bool PAD>
+template <typename VT, int NT, int MODE>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(step9_waves<VT, NT>()))) void k_step9(
     StepArgs a) {
   typedef Prod9<VT, NT, 1, 1> Prod;
@@ -36,7 +41,6 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(step9_waves
   const int tpw = a.tpw, wt = wave & (tpw - 1), wr = wave / tpw;  // tile and row of the wave
   const int sp = a.sp;
   const int nw = sp >> 6;
-  const int s_live = a.s_live > 0 ? a.s_live : sp;
   const VT *x = static_cast<const VT *>(a.x);
   const VT *prev = static_cast<const VT *>(a.prev);
   VT *out = static_cast<VT *>(a.out);
@@ -119,29 +123,24 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(step9_waves
     }
     const int pt = pg * tpw + wt;
     if (pt >= a.n_pt) continue;  // no such tile: the wave waits at the next flush
-    // first column of each access of this lane; PAD: a lane whose probes are all zero padding
-    // loads nothing (its inputs are zero)
+    // first column of each access of this lane
     int cc[NP];
-    bool live[NP];
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      cc[p] = pt * TW + p * (16 * PW) + n * PW;
-      live[p] = !PAD || cc[p] < s_live;
-    }
+    for (int p = 0; p < NP; ++p) cc[p] = pt * TW + p * (16 * PW) + n * PW;
     const int64_t r0 = rg * a.rows_per_wg;
     const int64_t r1 = min(a.nb, r0 + (int64_t)a.rows_per_wg);
     // PW probes of one scalar row of the output: shift, sources, moments, store, accumulator
-    auto finish = [&](int64_t row, int c, bool lv, const VT(&si)[PW], double *mo, double *mo2) {
+    auto finish = [&](int64_t row, int c, const VT(&si)[PW], double *mo, double *mo2) {
       const int64_t off = row * sp + c;
       VecN<VT, PW> pv, xv;
-      if (has_prev) pv = lv ? ldv_nt<VT, PW>(prev + off) : zerov<VT, PW>();
+      if (has_prev) pv = ldv_nt<VT, PW>(prev + off);
       VecN<VT, PW> sv[3];
       if (SRC) {
 #pragma unroll
         for (int t = 0; t < 3; ++t)
-          if (t < nsrc) sv[t] = lv ? ldv_nt<VT, PW>(srcp[t] + off) : zerov<VT, PW>();
+          if (t < nsrc) sv[t] = ldv_nt<VT, PW>(srcp[t] + off);
       }
-      if (m >= 2 || DBL) xv = lv ? ldv<VT, PW>(x + off) : zerov<VT, PW>();
+      if (m >= 2 || DBL) xv = ldv<VT, PW>(x + off);
       double r[PW];
       if (need_r) {
         if (a.sgn) {
@@ -149,7 +148,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(step9_waves
 #pragma unroll
           for (int q = 0; q < PW; ++q) r[q] = ((w >> ((c + q) & 63)) & 1ull) ? 1.0 : -1.0;
         } else {
-          const VecN<double, PW> rv = lv ? ldv<double, PW>(a.rden + off) : zerov<double, PW>();
+          const VecN<double, PW> rv = ldv<double, PW>(a.rden + off);
 #pragma unroll
           for (int q = 0; q < PW; ++q) r[q] = rv.v[q];
         }
@@ -177,7 +176,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(step9_waves
       }
       stv_nt<VT, PW>(out + off, o);
       if (m > 0) {
-        VecN<VT, PW> av = lv ? ldv_nt<VT, PW>(acc + off) : zerov<VT, PW>();
+        VecN<VT, PW> av = ldv_nt<VT, PW>(acc + off);
         av = add_terms<VT, PW>(av, m, al, pv, xv, o);
         stv_nt<VT, PW>(acc + off, av);
       }
@@ -185,7 +184,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(step9_waves
     for (int64_t I = r0 + wr; I < r1; I += kWaves / tpw) {
       const int64_t beg = sld(a.row_ptr + I), end = sld(a.row_ptr + I + 1);
       Prod pr;
-      pr.row(mat, a.col, xs, beg, end, sp * (int)sizeof(VT), lane, live, Prod::lane_bytes(lane, sp, pt), hw);
+      pr.row(mat, a.col, xs, beg, end, sp * (int)sizeof(VT), lane, Prod::lane_bytes(lane, sp, pt), hw);
       VT s8[NT];
 #pragma unroll
       for (int c = 0; c < NT; ++c) s8[c] = pr.row8(0, c);
@@ -196,24 +195,22 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(step9_waves
           VT si[PW];
 #pragma unroll
           for (int e = 0; e < PW; ++e) si[e] = pr.group_row(0, q, p * PW + e);
-          finish(I * 9 + 4 * q + grp, cc[p], live[p], si, mom + p * PW, mom2 + p * PW);
+          finish(I * 9 + 4 * q + grp, cc[p], si, mom + p * PW, mom2 + p * PW);
         }
       // row 8: lane group p takes access p
       if (grp < NP) {
         VT si[PW];
         int c = cc[0];
-        bool lv = live[0];
 #pragma unroll
         for (int e = 0; e < PW; ++e) si[e] = s8[e];
 #pragma unroll
         for (int p = 1; p < NP; ++p)
           if (grp == p) {
             c = cc[p];
-            lv = live[p];
 #pragma unroll
             for (int e = 0; e < PW; ++e) si[e] = s8[p * PW + e];
           }
-        finish(I * 9 + 8, c, lv, si, mom8, mom82);
+        finish(I * 9 + 8, c, si, mom8, mom82);
       }
     }
   }
@@ -227,7 +224,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(step9_waves
 // Per chunk of two blocks a wave loads the H_hat blocks with coalesced loads into its LDS slice
 // and issues the neighbour-row gathers; the FMAs then read the entries back as LDS broadcasts.
 // ---------------------------------------------------------------------------
-template <int MODE, bool PAD>
+template <int MODE>
 __global__ __launch_bounds__(kWG) void k_step9_wide(StepArgs a) {
   typedef float VT;
   constexpr int PPL = 4, U = 2, BD = 9, BB = 81;
@@ -236,7 +233,6 @@ __global__ __launch_bounds__(kWG) void k_step9_wide(StepArgs a) {
   const int lane = threadIdx.x & 63;
   const int sp = a.sp;
   const int nw = sp >> 6;
-  const int s_live = a.s_live > 0 ? a.s_live : sp;
   const VT *__restrict__ x = static_cast<const VT *>(a.x);
   const VT *prev = static_cast<const VT *>(a.prev);
   VT *out = static_cast<VT *>(a.out);
@@ -289,9 +285,6 @@ __global__ __launch_bounds__(kWG) void k_step9_wide(StepArgs a) {
       cur_pt = pt;
     }
     const int c0 = pt * (64 * PPL) + lane * PPL;
-    // PAD: a lane whose probes are all zero padding loads nothing (its inputs are
-    // zero); without padding columns the predicate is compiled out
-    const bool live = !PAD || c0 < s_live;
     const int64_t r0 = rg * a.rows_per_wg;
     const int64_t r1 = min(a.nb, r0 + (int64_t)a.rows_per_wg);
     // one scalar row of the output: shift, sources, moments, store, accumulator
@@ -299,15 +292,14 @@ __global__ __launch_bounds__(kWG) void k_step9_wide(StepArgs a) {
         const int64_t row = I * BD + i;
         const int64_t off = row * sp + c0;
         VecN<VT, PPL> pv, xs;
-        if (has_prev)
-          pv = live ? ldv_nt<VT, PPL>(prev + off) : zerov<VT, PPL>();
+        if (has_prev) pv = ldv_nt<VT, PPL>(prev + off);
         VecN<VT, PPL> sv[3];
         if (SRC) {
 #pragma unroll
           for (int t = 0; t < 3; ++t)
-            if (t < nsrc) sv[t] = live ? ldv_nt<VT, PPL>(srcp[t] + off) : zerov<VT, PPL>();
+            if (t < nsrc) sv[t] = ldv_nt<VT, PPL>(srcp[t] + off);
         }
-        if (m >= 2 || DBL) xs = live ? ldv<VT, PPL>(x + off) : zerov<VT, PPL>();
+        if (m >= 2 || DBL) xs = ldv<VT, PPL>(x + off);
         double r[PPL];
         if (need_r) {
           if (a.sgn) {
@@ -315,7 +307,7 @@ __global__ __launch_bounds__(kWG) void k_step9_wide(StepArgs a) {
 #pragma unroll
             for (int q = 0; q < PPL; ++q) r[q] = ((w >> ((c0 + q) & 63)) & 1ull) ? 1.0 : -1.0;
           } else {
-            const VecN<double, PPL> rv = live ? ldv<double, PPL>(a.rden + off) : zerov<double, PPL>();
+            const VecN<double, PPL> rv = ldv<double, PPL>(a.rden + off);
 #pragma unroll
             for (int q = 0; q < PPL; ++q) r[q] = rv.v[q];
           }
@@ -343,7 +335,7 @@ __global__ __launch_bounds__(kWG) void k_step9_wide(StepArgs a) {
         }
         stv_nt<VT, PPL>(out + off, o);
         if (m > 0) {
-          VecN<VT, PPL> av = live ? ldv_nt<VT, PPL>(acc + off) : zerov<VT, PPL>();
+          VecN<VT, PPL> av = ldv_nt<VT, PPL>(acc + off);
           av = add_terms<VT, PPL>(av, m, al, pv, xs, o);
           stv_nt<VT, PPL>(acc + off, av);
         }
@@ -373,7 +365,7 @@ __global__ __launch_bounds__(kWG) void k_step9_wide(StepArgs a) {
           if (u == 0 || nz + u < end) {
 #pragma unroll
             for (int j = 0; j < BD; ++j)
-              xv[u][j] = live ? ldv<VT, PPL>(x + (J[u] * BD + j) * sp + c0) : zerov<VT, PPL>();
+              xv[u][j] = ldv<VT, PPL>(x + (J[u] * BD + j) * sp + c0);
           }
         }
       };
@@ -420,49 +412,47 @@ __global__ __launch_bounds__(kWG) void k_step9_wide(StepArgs a) {
 
 namespace {
 
-template <typename VT, int NT, bool PAD>
+template <typename VT, int NT>
 const void *step9_fn(int mode) {
   switch (mode) {
-    case 0: return (const void *)k_step9<VT, NT, 0, PAD>;
-    case 1: return (const void *)k_step9<VT, NT, 1, PAD>;
-    case 2: return (const void *)k_step9<VT, NT, 2, PAD>;
-    case 3: return (const void *)k_step9<VT, NT, 3, PAD>;
+    case 0: return (const void *)k_step9<VT, NT, 0>;
+    case 1: return (const void *)k_step9<VT, NT, 1>;
+    case 2: return (const void *)k_step9<VT, NT, 2>;
+    case 3: return (const void *)k_step9<VT, NT, 3>;
     default: return nullptr;
   }
 }
 
-template <typename VT, bool PAD>
+template <typename VT>
 const void *step9_fn_t(int nt, int mode) {
   switch (nt) {
-    case 1: return step9_fn<VT, 1, PAD>(mode);
-    case 2: return step9_fn<VT, 2, PAD>(mode);
-    case 4: return step9_fn<VT, 4, PAD>(mode);
+    case 1: return step9_fn<VT, 1>(mode);
+    case 2: return step9_fn<VT, 2>(mode);
+    case 4: return step9_fn<VT, 4>(mode);
     default: return nullptr;
   }
 }
 
-template <bool PAD>
 const void *step9_wide_fn(int mode) {
   switch (mode) {
-    case 0: return (const void *)k_step9_wide<0, PAD>;
-    case 1: return (const void *)k_step9_wide<1, PAD>;
-    case 2: return (const void *)k_step9_wide<2, PAD>;
-    case 3: return (const void *)k_step9_wide<3, PAD>;
+    case 0: return (const void *)k_step9_wide<0>;
+    case 1: return (const void *)k_step9_wide<1>;
+    case 2: return (const void *)k_step9_wide<2>;
+    case 3: return (const void *)k_step9_wide<3>;
     default: return nullptr;
   }
 }
 
 // nt = 16 FP32: k_step9_wide
-const void *select_step9(int precision, int nt, int mode, bool pad) {
-  if (precision == 1 && nt == 16) return pad ? step9_wide_fn<true>(mode) : step9_wide_fn<false>(mode);
-  if (precision == 0) return pad ? step9_fn_t<double, true>(nt, mode) : step9_fn_t<double, false>(nt, mode);
-  return pad ? step9_fn_t<float, true>(nt, mode) : step9_fn_t<float, false>(nt, mode);
+const void *select_step9(int precision, int nt, int mode) {
+  if (precision == 1 && nt == 16) return step9_wide_fn(mode);
+  return precision == 0 ? step9_fn_t<double>(nt, mode) : step9_fn_t<float>(nt, mode);
 }
 
 }  // namespace
 
 int step9_blocks_per_cu(int precision, int nt) {
-  const void *f = select_step9(precision, nt, 0, false);
+  const void *f = select_step9(precision, nt, 0);
   if (!f) return 0;
   int nblk = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nblk, f, kWG, 0) != hipSuccess) return 0;
@@ -470,7 +460,7 @@ int step9_blocks_per_cu(int precision, int nt) {
 }
 
 hipError_t launch_step9(int precision, int nt, const StepArgs &a, hipStream_t s) {
-  const void *f = select_step9(precision, nt, step_mode(a), a.s_live > 0 && a.s_live < a.sp);
+  const void *f = select_step9(precision, nt, step_mode(a));
   if (!f || a.grid < 8 || (a.grid & 7) || a.n_pt * 16 * nt > a.sp || (a.tpw != 1 && a.tpw != 2))
     return hipErrorInvalidValue;
   void *args[] = {const_cast<StepArgs *>(&a)};

@@ -146,32 +146,26 @@ struct Prod9 {
     }
   }
 
-  // requests the rows of K step T; live: the columns of an access are not all padding
+  // requests the rows of K step T
   template <int T>
-  static __device__ __forceinline__ void load_step(Rows &ch, const Bases &bs, int rowb, const bool (&live)[NP],
-                                                   uint32_t vb) {
+  static __device__ __forceinline__ void load_step(Rows &ch, const Bases &bs, int rowb, uint32_t vb) {
 #pragma unroll
     for (int pl = 0; pl < PL; ++pl) {
       GlobalBytes src;
       if constexpr (T == 8) src = bs.last[pl];
       else src = bs.base[pl][T / 2] + (T % 2 ? vb + 4u * (uint32_t)rowb : vb);
 #pragma unroll
-      for (int p = 0; p < NP; ++p) ch.x[T][pl * NP + p] = gather(src, p, live[p]);
+      for (int p = 0; p < NP; ++p) ch.x[T][pl * NP + p] = gather(src, p);
     }
   }
 
   // access p of a gathered row
-  static __device__ __forceinline__ VecN<VT, PW> gather(GlobalBytes src, int p, bool live) {
+  static __device__ __forceinline__ VecN<VT, PW> gather(GlobalBytes src, int p) {
     typedef VT V __attribute__((ext_vector_type(PW)));
-    VecN<VT, PW> r = zerov<VT, PW>();
-    if (live) {
-      const V v = *reinterpret_cast<const __attribute__((address_space(1))) V *>(src + p * (16 * PW * (int)sizeof(VT)));
+    const V v = *reinterpret_cast<const __attribute__((address_space(1))) V *>(src + p * (16 * PW * (int)sizeof(VT)));
+    VecN<VT, PW> r;
 #pragma unroll
-      for (int q = 0; q < PW; ++q) {
-        if constexpr (PW == 1) r.v[q] = v[0];
-        else r.v[q] = v[q];
-      }
-    }
+    for (int q = 0; q < PW; ++q) r.v[q] = v[q];
     return r;
   }
 
@@ -324,8 +318,7 @@ struct Prod9 {
   // chunk of fewer than four blocks gathers its first block's rows again (lines already on their
   // way) and multiplies them by zeros: one path without branches.
   __device__ __forceinline__ void row(const VT *const (&mat)[NM], const int32_t *col, const VT *const (&x)[PL],
-                                      int64_t beg, int64_t end, int rowb, int lane, const bool (&live)[NP],
-                                      uint32_t vb, VT *hw) {
+                                      int64_t beg, int64_t end, int rowb, int lane, uint32_t vb, VT *hw) {
     clear();
     if (beg >= end) return;
     int32_t J[kB9];
@@ -343,7 +336,7 @@ struct Prod9 {
     load_entries(h, mat, beg, lane);
     columns(J, col, beg);
     locate(bs, J, x, blocks(beg), rowb, lane, vb);
-    for_steps([&](auto tc) { load_step<decltype(tc)::value>(ch, bs, rowb, live, vb); });
+    for_steps([&](auto tc) { load_step<decltype(tc)::value>(ch, bs, rowb, vb); });
     int64_t nz = beg;
     columns(J, col, nz + kB9 < end ? nz + kB9 : nz);
     for (; nz + kB9 < end; nz += kB9) {
@@ -352,7 +345,7 @@ struct Prod9 {
       locate(bs, J, x, blocks(nz + kB9), rowb, lane, vb);
       columns(J, col, nz + 2 * kB9 < end ? nz + 2 * kB9 : nz);
       __builtin_amdgcn_sched_barrier(0);
-      use(ch, hw, lane, [&](auto tc) { load_step<decltype(tc)::value>(ch, bs, rowb, live, vb); });
+      use(ch, hw, lane, [&](auto tc) { load_step<decltype(tc)::value>(ch, bs, rowb, vb); });
     }
     put(nz);
     use(ch, hw, lane, [](auto) {});

@@ -62,8 +62,8 @@ struct StepArgs {
   int tpw;                 // FP64/FP32 9x9 steps: probe tiles of a block row per workgroup (1, 2)
   int hsplit;              // BF16 steps: the pack holds hi and lo BF16 parts of H_hat
   // probe columns at or past s_live are zero in every input vector (dense probes,
-  // whose padding columns are zero): a lane whose probes all lie there loads
-  // nothing and stores zeros.  0 = every column is live.
+  // whose padding columns are zero): in the 1x1 and BF16 steps a lane whose probes all lie
+  // there loads nothing and stores zeros.  0 = every column is live.
   int s_live;
 };
 
