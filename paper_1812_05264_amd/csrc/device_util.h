@@ -44,8 +44,8 @@ struct Sched {
   }
   __device__ bool more() const { return i < hi; }
   // tile and row group move along with the unit: a division for each took as many instructions as a
-  // row of a 7-point stencil (steps of 1x1 blocks, us: 110,592 rows and 64 probes, FP64 52.3 -> 50.2, 32,768
-  // and 100, FP32 19.3 -> 18.7; 262,144 and 256, FP64 404 -> 402)
+  // row of a 7-point stencil (steps of 1x1 blocks, us: 110,592 rows and 64 probes, FP64 51.3 -> 49.7, 32,768
+  // and 100, FP32 18.5 -> 18.1; 262,144 and 256, FP64 444.0 -> 441.5)
   __device__ void next() {
     i += stride;
     if (rev) {

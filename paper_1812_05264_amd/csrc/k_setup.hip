@@ -177,7 +177,8 @@ hipError_t launch_probe_pack(const double *rden, int64_t n, int s_real, int sp, 
 // The two ways round differently in the last bit, which means nothing to FP64 and FP32 vectors. The BF16
 // gradient rounds z_j to eight bits in every step, and a last bit in its sources decides some of those
 // roundings: it moved the forces by the path's whole error (1.1e-3 at 16,000 atoms, 1,000 terms). Their
-// coefficients therefore keep one order of sums for good; the call has milliseconds for the 12 us more.
+// coefficients therefore keep one order of sums for good, at 1,084 us against 124 for 8,000 terms (0.03% of
+// the 16,000-atom call that they belong to).
 template <bool HALF>
 __global__ __launch_bounds__(kWG) void k_coef_samples(double e_min, double e_max, double T,
                                                       double mu, int64_t nq,
